@@ -35,7 +35,8 @@ struct les_batch {
   int totals[BK_NKIND] = {0};
   size_t sh_x = 0, sh_y = 0, sh_z = 0;
   bool dirty = true;
-  int tune_kc = 0;   // 0: per-box default; else planes per dynamic-model chunk
+  int tune_kc = 0;   // 0: def_kc; else planes per dynamic-model chunk
+  int def_kc = 8;    // default chunk (at most a box's planes)
   int tune_l = 0;    // 0: default lines per FFT block; else this power of two
   double tune_cfl_graph = -1.0;   // cfl the recorded graph was captured with
   hipGraph_t graph = nullptr;
@@ -113,7 +114,7 @@ les_status prepare(les_batch* b) {
     d.pbx = fft_pairs_per_block(nx);
     d.ly = b->tune_l ? std::min(b->tune_l, pow2_at_most(std::max(1, 2048 / ny))) : fft_lines_per_block(ny);
     d.lz = b->tune_l ? std::min(b->tune_l, pow2_at_most(std::max(1, 2048 / nz))) : fft_lines_per_block(nz);
-    d.kc = b->tune_kc ? std::min(b->tune_kc, nz) : c.dsm_kc;
+    d.kc = std::min(b->tune_kc ? b->tune_kc : b->def_kc, nz);
     d.pkc = c.pred_kc;
     d.sgs = c.cfg.sgs;
     auto set = [&](int kind, int x, int y, int z) {
@@ -222,6 +223,25 @@ les_status les_batch_init(const les_config* cfgs, int nbox, void* hip_stream, le
     b->woff.push_back(wo);
     fo = al256(fo + (size_t)lf.bytes);
     wo = al256(wo + (size_t)lw.bytes);
+  }
+  // dynamic-model chunks: the length with the fewest plane iterations of the whole launch, all boxes'
+  // chunks spread over the resident blocks, plus one chunk for its uneven end
+  const bool fp64 = b->prec != LES_MIXED;
+  double best = 0.0;
+  for (int kc = 4; kc <= 64; kc += 4) {
+    double work = 0.0;
+    int longest = 0;
+    for (int i = 0; i < nbox; ++i) {
+      const int nz = cfgs[i].nz, k = std::min(kc, nz), ty = dsm_tile_rows(fp64);
+      const double blocks = (double)((cfgs[i].nx + 31) / 32) * ((cfgs[i].ny + ty - 1) / ty) * ((nz + k - 1) / k);
+      work += blocks * (k + DSM_WARM);
+      longest = std::max(longest, k + DSM_WARM);
+    }
+    const double cost = work / (256 * dsm_blocks_per_cu(fp64)) + longest;
+    if (best == 0.0 || cost < best) {
+      best = cost;
+      b->def_kc = kc;
+    }
   }
   b->ftotal = fo;
   b->desc_off = wo;

@@ -209,9 +209,8 @@ size_t carve(Ctx& c, char* base) {
   t.nblk_xy = ((f.nx + 31) / 32) * ((f.ny + 7) / 8);
   {
     // z chunk lengths in units of 32 x 8 tiles on 256 CUs: whole rounds of resident blocks, at
-    // least 8 planes (the dynamic model's FP64 block covers two such tiles, one block per CU;
-    // the learned-closure inference runs four blocks per CU on chunks sized for three, which
-    // measured faster than chunks for four)
+    // least 8 planes (the learned-closure inference runs four blocks per CU on chunks sized for
+    // three, which measured faster than chunks for four)
     auto chunk = [&](int64_t slots) {
       const int64_t want = ((int64_t)n * t.nblk_xy + slots - 1) / slots;
       return (int)std::max<int64_t>(std::min<int64_t>(8, n), std::min<int64_t>(n, want));
@@ -233,7 +232,21 @@ size_t carve(Ctx& c, char* base) {
       const int kc = whole_rounds(slots);
       return kc > 0 ? kc : chunk(slots);
     };
-    c.dsm_kc = chunk(512);
+    {
+      // dynamic model: the z chunks that take the fewest plane iterations, rounds of resident blocks times the
+      // planes of a chunk and its warm-up.  Whole chunks of one length are not always best: the 512x80x80 duct
+      // (80 tiles) ran its last quarter round on its own with chunks of 25 planes, 3 x 27 fill the CUs once.
+      const bool fp64 = f.precision != LES_MIXED;
+      const int64_t tiles = (int64_t)((f.nx + 31) / 32) * ((f.ny + dsm_tile_rows(fp64) - 1) / dsm_tile_rows(fp64));
+      const int64_t slots = 256 * dsm_blocks_per_cu(fp64);
+      int64_t best = 0;
+      for (int64_t kc = n; kc >= std::min(4, n); --kc) {
+        const int64_t cost = (tiles * ((n + kc - 1) / kc) + slots - 1) / slots * (kc + DSM_WARM);
+        if (best != 0 && cost >= best) continue;
+        best = cost;
+        c.dsm_kc = (int)kc;
+      }
+    }
     c.mlp_kc = chunk(768);
     // z-marching predictor: 32 x 16 tiles, at one 512-thread block per CU in FP64 and two in
     // FP32, fetch less halo than 32 x 8 tiles at three (FP64) or four (FP32) blocks per CU

@@ -50,6 +50,10 @@ struct PlaneLoader {
       : r(__builtin_amdgcn_make_buffer_rsrc((void*)(base + plane * sxy), (short)0, (int)(sxy * (int64_t)sizeof(T)),
                                             0x00020000)) {}
   __device__ T operator()(int off) const;
+  __device__ void store(int off, T x) const;
+  // straight to LDS, no register between: 16 bytes per lane for double, 4 for float, lane l's at dst + l
+  // such parts (dst uniform across the wave), from byte offset boff
+  __device__ void to_lds(T* dst, int boff) const;
 };
 template <>
 __device__ inline double PlaneLoader<double>::operator()(int off) const {
@@ -58,6 +62,26 @@ __device__ inline double PlaneLoader<double>::operator()(int off) const {
 template <>
 __device__ inline float PlaneLoader<float>::operator()(int off) const {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off * 4, 0, 0));
+}
+
+template <>
+__device__ inline void PlaneLoader<double>::store(int off, double x) const {
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), r, off * 8, 0, 0);
+}
+template <>
+__device__ inline void PlaneLoader<float>::store(int off, float x) const {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, off * 4, 0, 0);
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+template <>
+__device__ inline void PlaneLoader<double>::to_lds(double* dst, int boff) const {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, boff, 0, 0, 0);
+}
+template <>
+__device__ inline void PlaneLoader<float>::to_lds(float* dst, int boff) const {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 4, boff, 0, 0, 0);
 }
 
 // Workgroup barrier that orders LDS only: it waits for the wave's LDS operations, not for
@@ -90,9 +114,12 @@ __host__ __device__ inline void tile_shape(int nx, int ny, int& bx, int& by) {
 __host__ __device__ inline int64_t idx3(const GridP& g, int k, int j, int i) {
   return ((int64_t)k * g.nys + j) * g.nx + i;
 }
-// Rows of the x-y tiles of the fused dynamic-model kernel (32 columns wide): 16 in FP64 (not in
-// ducts), 8 in FP32 and in ducts.
+// Rows of the x-y tiles of the fused dynamic-model kernel (32 columns wide): 16 in FP64, 8 in FP32.
 constexpr int dsm_tile_rows(bool fp64) { return fp64 ? 16 : 8; }
+// Blocks of that kernel a CU holds: the LDS of an FP64 block is 156 KB, that of an FP32 block 46 KB
+constexpr int dsm_blocks_per_cu(bool fp64) { return fp64 ? 1 : 3; }
+// Planes its z march spends before the first plane it puts out
+constexpr int DSM_WARM = 3;
 
 // XCD-aware tile order.  Workgroups are dispatched to the 8 XCDs in turn by linear index;
 // when a plane holds a multiple of 8 tiles, XCD x gets the contiguous band of tiles

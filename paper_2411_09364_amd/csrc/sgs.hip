@@ -361,37 +361,557 @@ __global__ void __launch_bounds__(256) k_dsm_reduce(GridP g, const double* part,
 }
 
 // ============================================================================ fused dynamic model
-// One z-marching pass per (32 x 8 tile, chunk of planes) computing |S| and the plane sums
+// One z-marching pass per (32-wide tile, chunk of planes) computing |S| and the plane sums
 // of L_ij M_ij and M_ij M_ij, reading u, v, w once (halo 2) and writing |S| once.
-//   LDS: velocity of planes p, p + 1 on the tile + 2 halo (strain ghosts substituted),
-//        the 15 filter inputs (u_i, u_i u_j, |S| S_ij at cell centres) of plane p on the
-//        tile + 1 halo, stored in pairs (one 16-byte read per pair in the filter), the
-//        test-filtered staggered velocity of two planes on the tile + 1 halo.
-//   Registers: the z pass of the test filter as running sums over the thread's cell; the
-//        upper z-edge terms of the off-diagonal strain and w of the previous plane at the
-//        thread's points, which are the lower terms of the plane above (so only planes k and
-//        k + 1 are needed to form the strain of plane k).
-// The stage of plane p forms the filter inputs of plane p from velocity planes p, p + 1 and
-// completes the filtered velocity of plane p - 1; once stage p is done the cell values of plane
-// p - 1 are final (z pass of the test filter, S~ from the filtered velocity, L and M).
-// Wall rules as in the rest of the dynamic model: on the first off-wall layers the z pass of
-// the filter is the identity (the index-space extrapolation of the neighbour reduces to it),
-// filtered-velocity ghosts follow the strain ghost rule, alpha^2 = 4^(2/3) there.
-// Tiles of 32 x 16 cells in FP64 (one 512-thread block per CU: the LDS of a block is about
-// 140 KB, and the halo is a smaller share of the tile) and 32 x 8 in FP32 (three 256-thread
-// blocks per CU) and in the duct variant (YW; two blocks per CU in FP64).
+//   LDS: velocity of one plane on the tile + 2 halo, the 12 filter inputs (u_i u_j, |S| S_ij at
+//        cell centres) of one plane on the tile + 1 halo, their x sums on the tile + 1 halo in y,
+//        and the test-filtered staggered velocity of one plane on the tile + 1 halo.
+//   Registers: at the thread's cell what the plane above needs of this one (Strain below) and the
+//        running z sums of the test filter.  The first threads have one halo point as well, whose
+//        march is kept in LDS: in registers every thread would hold room for it.
+// Iteration q reads the 3 x 3 neighbourhood of velocity plane q once per point, for the
+// in-plane strain terms of plane q and the x-y test filter together; with the z differences that
+// it completes it finishes the strain and filter inputs of plane p = q - 1, the filtered velocity
+// of plane p and, from that, the strain of the filtered velocity, L and M of plane k = q - 2.
+// The test filter runs unnormalised, (1, 2, 1) per direction (exact powers of two, folded into the
+// final sums), x first and then y: two of the three x (y) values come from LDS.
+// The filtered centre velocities are the two-point means of the filtered staggered ones (both
+// are linear), except where the two filters differ: w next to the z walls (the z pass of a centred
+// quantity is the identity there) and v next to the y walls of a duct.
+// Wall rules: on the first off-wall layers the z pass of the filter is the identity (the index-space
+// extrapolation of the neighbour reduces to it), alpha^2 = 4^(2/3) there; the strain ghost rule
+// of either velocity makes the z difference across the wall that of the next edge inward (wall
+// model, linear extrapolation) or twice the cell's own value (no-slip, odd).
+// Bound by latency at two waves per SIMD in FP64 (156 KB of LDS and 256 registers: one block of 32 x 16
+// cells per CU; VALU busy 36 %, LDS 45 %) and by VALU issue at three in FP32 (32 x 8 cells, three blocks per
+// CU).  512x256x128 FP64 with the wall model: 601 -> 505 us, against 596 us for 15 inputs through a 9-point
+// filter with all four edges of a cell worked out; 256x128x96: 127 -> 112; 64 boxes of 32^3 to 96^3 in FP32:
+// 4614 -> 3909 us a step; 512x80x80 duct: 217 -> 147.  Measured and dropped in FP64: 32 x 8 tiles at two blocks per CU (572: the halo's
+// share), x sums by lane shifts in place of LDS (508), separate waves for halo points on 32 x 12 tiles (612)
+// or for the model on 16 waves (884, spills), the halo points after the first barrier (586).
 namespace fused {
 constexpr int TX = 32;
-constexpr int NQ = 15;   // filter inputs per cell
-template <typename T, bool YW = false>
+constexpr int NQ = 12;   // filter inputs per cell
+template <typename T>
 struct Tile {
-  static constexpr int TY = dsm_tile_rows(sizeof(T) == 8 && !YW), NT = TX * TY, WV = NT / 64;
+  static constexpr int TY = dsm_tile_rows(sizeof(T) == 8), NT = TX * TY, WV = NT / 64;
+  static constexpr int RX2 = TX + 4, RY2 = TY + 4, N2 = RX2 * RY2;  // halo 2
+  static constexpr int RX1 = TX + 2, RY1 = TY + 2, N1 = RX1 * RY1;  // halo 1
+  static constexpr int NROW = 2 * TX, NHALO = NROW + 2 * RY1;        // halo-1 points around the tile
+  static constexpr int WEU = sizeof(T) == 8 ? 2 : 3;                 // waves per SIMD
+};
+// inputs per 16-byte LDS access
+template <typename T>
+struct alignas(16) Pack {
+  static constexpr int N = 16 / sizeof(T);
+  T x[N];
+};
+}  // namespace fused
+
+// Terms of one point that a z march of the strain carries (edge terms scaled by 1/8: the mean of
+// four edge values of half sums): of plane q - 1 the in-plane strain, U = u_i + u_{i-1},
+// V = v_j + v_{j-1}, w on its upper face and the x and y differences of w there; of plane q - 2
+// the upper z-edge terms (ex, ey) and w.  The two-point sums replace the four edges of a cell:
+// (u_{j+1} - u_j) + (u_j - u_{j-1}) and the like telescope.
+template <typename T>
+struct Strain {
+  static constexpr int N = 11;
+  T s11, s22, s12, U, V, w, wx, wy, ex, ey, wl;
+};
+// In-plane terms of a plane at one point, component by component, from the 3 x 3 neighbourhoods
+// ([row][column]); s12 takes u's share first, then v's.
+template <typename T>
+__device__ __forceinline__ void strain_inplane(int c, const T (&a)[3][3], T rdx, T rdy, Strain<T>& n) {
+#pragma clang fp contract(on)
+  const T rdx8 = (T)0.125 * rdx, rdy8 = (T)0.125 * rdy;
+  if (c == 0) {
+    n.U = a[1][1] + a[1][0];
+    n.s11 = (a[1][1] - a[1][0]) * rdx;
+    n.s12 = ((a[2][1] + a[2][0]) - (a[0][1] + a[0][0])) * rdy8;
+  } else if (c == 1) {
+    n.V = a[1][1] + a[0][1];
+    n.s22 = (a[1][1] - a[0][1]) * rdy;
+    n.s12 = ((a[1][2] + a[0][2]) - (a[1][0] + a[0][0])) * rdx8 + n.s12;
+  } else {
+    n.w = a[1][1];
+    n.wx = (a[1][2] - a[1][0]) * rdx8;
+    n.wy = (a[2][1] - a[0][1]) * rdy8;
+  }
+}
+
+// Upper z-edge terms of plane q - 1 from plane q (n) and the march up to plane q - 1 (c)
+template <typename T>
+__device__ __forceinline__ void strain_edges(const Strain<T>& c, const Strain<T>& n, T rdzc8, T& ex, T& ey) {
+#pragma clang fp contract(on)
+  ex = (n.U - c.U) * rdzc8 + c.wx;
+  ey = (n.V - c.V) * rdzc8 + c.wy;
+}
+
+// x of another lane of the same row of 16 lanes, by a DPP lane pattern
+template <int CTRL>
+__device__ inline double dpp_f64(double x) {
+  const int lo = __double2loint(x), hi = __double2hiint(x);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, false));
+}
+// sum over each row of 16 lanes, a 4-level tree (partners at lane distance 1 and 2 in a quad,
+// then the mirrored half-row and row): every lane of a row holds the same bits
+__device__ inline double row_sum(double x) {
+  x = x + dpp_f64<0xB1>(x);    // quad permutation 1 0 3 2
+  x = x + dpp_f64<0x4E>(x);    // quad permutation 2 3 0 1
+  x = x + dpp_f64<0x141>(x);   // half-row mirror
+  x = x + dpp_f64<0x140>(x);   // row mirror
+  return x;
+}
+// lane L's value of x, uniform across the wave
+__device__ inline double lane_f64(double x, int L) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), L),
+                          __builtin_amdgcn_readlane(__double2loint(x), L));
+}
+// Both sums over each half wave (32 lanes) with one row tree: rows 0 and 2 of a take what rows
+// 1 and 3 hold, rows 1 and 3 the same of b, then row_sum.  The result in rows 0..3: a of the
+// lower half, b of the lower half, a of the upper half, b of the upper half.
+__device__ inline double half_sums(double a, double b) {
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  const v2u lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const v2u hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return row_sum(__hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]));
+}
+
+template <typename T>
+__device__ inline T strain_norm(const T s[6]) {
+#pragma clang fp contract(on)
+  const T d = s[0] * s[0] + s[1] * s[1] + s[2] * s[2];
+  const T e = s[3] * s[3] + s[4] * s[4] + s[5] * s[5];
+  return sqrt((T)2 * d + (T)4 * e);
+}
+
+// YW (ducts, walls in y too): the y pass of the test filter is the identity on the first and
+// last rows for y-centred quantities (u, w and the cell quantities), v~ vanishes on and
+// beyond the y wall faces, the y ghost rows of u~ and w~ follow the strain ghost rule, alpha^2
+// counts the filter's dimensions per cell, and the partial sums are per x line (one per row
+// of each wave: 32 lanes) instead of per wave.
+template <typename T, bool YW, int ZBC>
+__device__ __forceinline__ void dsm_fused_body(dim3 bid, int gdx, int gdy, GridP g, const T* __restrict__ u,
+                                               const T* __restrict__ v, const T* __restrict__ w,
+                                               T* __restrict__ nut, double* __restrict__ part, int kc,
+                                               const int* __restrict__ gate) {
+#pragma clang fp contract(on)
+  using TL = fused::Tile<T>;
+  using Pack = fused::Pack<T>;
+  constexpr int TX = fused::TX, TY = TL::TY, NT = TL::NT, WV = TL::WV, NQ = fused::NQ, PN = Pack::N, NP = NQ / PN;
+  constexpr int RX2 = TL::RX2, N2 = TL::N2, RX1 = TL::RX1, RY1 = TL::RY1, N1 = TL::N1, NROW = TL::NROW,
+                NHALO = TL::NHALO;
+  if (gate != nullptr && gate[0] == 0) return;   // learned closure: no point fell back
+  __shared__ T vel[3][N2];           // velocity plane q
+  __shared__ Pack qb[NP][N1];        // filter inputs of plane p
+  __shared__ Pack xb[NP][RY1 * TX];  // their x sums
+  __shared__ T ut[3][N1];            // filtered velocity of plane p (times 64)
+  __shared__ T hst[Strain<T>::N + 6][NHALO];   // march of the halo points
+  int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
+  const int i0 = bid.x * TX, j0 = bid.y * TY;
+  const int nz = g.nz;
+  const int kb = 1 + bid.z * kc;
+  const int ke = min(nz, kb + kc - 1);
+  constexpr bool per = ZBC == LES_ZBC_PERIODIC;
+  constexpr bool wm = ZBC == LES_ZBC_WALLMODEL;
+  const int ntile = gdx * gdy;
+  const int tile = bid.y * gdx + bid.x;
+  const T rdx = (T)g.rdx, rdy = (T)g.rdy;
+  const int64_t sxy = g.sxy;
+  auto phys = [&](int q) {  // logical plane -> stored plane (periodic wrap of interior planes)
+    if (!per) return q;
+    int m = (q - 1) % nz;
+    if (m < 0) m += nz;
+    return m + 1;
+  };
+  // The velocity plane under way.  FP64: straight from memory to LDS (DIRECT), into the one buffer, issued when
+  // the block has done with the plane before; no registers hold it, where the compiler would spill just those
+  // and so wait for the loads at once.  16 bytes per lane, a pair of columns: the tile's first column i0 - 2 and
+  // nx are even, so pairs stay whole and aligned across the wrap.  FP32: in registers between its fetch and its
+  // commit to LDS, a whole iteration, with one element per lane.
+  // lofs: byte offset in a plane of the thread's parts of the tile + 2 halo (tiles may exceed the grid: wrap);
+  // threads past the halo load nothing (DIRECT), or offset 0 and commit nothing.
+  constexpr bool DIRECT = sizeof(T) == 8;
+  constexpr int LC = DIRECT ? 2 : 1;                    // columns per lane
+  constexpr int NPART = N2 / LC, NL = (NPART + NT - 1) / NT;
+  int lofs[NL];
+  T ra[3][DIRECT ? 1 : NL];
+  for (int r = 0; r < NL; ++r) {
+    const int e = (tid + r * NT) * LC;
+    int i = (i0 - 2 + e % RX2) % g.nx, j = (j0 - 2 + e / RX2) % g.nys;
+    if (i < 0) i += g.nx;
+    if (j < 0) j += g.nys;
+    lofs[r] = e < N2 ? (j * g.nx + i) * (int)sizeof(T) : 0;
+  }
+  auto fetch = [&](int q) {
+    const int pq = phys(q);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const PlaneLoader<T> ld(c == 0 ? u : (c == 1 ? v : w), pq, sxy);
+#pragma unroll
+      for (int r = 0; r < NL; ++r) {
+        if constexpr (DIRECT) {
+          const int first = __builtin_amdgcn_readfirstlane(tid) + r * NT;
+          if (tid + r * NT < NPART) ld.to_lds(&vel[c][first * LC], lofs[r]);
+        } else {
+          ra[c][r] = ld(lofs[r] / (int)sizeof(T));
+        }
+      }
+    }
+  };
+  auto commit = [&]() {
+#pragma unroll
+    for (int r = 0; r < NL; ++r)
+      if (tid + r * NT < N2)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) vel[c][tid + r * NT] = ra[c][r];
+  };
+  // ducts with the wall model: u and w on the y ghost rows of the committed plane, extrapolated
+  // from the two rows inward (strain ghosts); only blocks at a y wall hold such rows
+  const bool ywall_block = YW && wm && (j0 == 0 || j0 + TY + 1 >= g.ny);
+  auto extrapolate_rows = [&]() {
+    for (int e = tid; e < 4 * RX2; e += NT) {
+      const int c = e / (2 * RX2) * 2, x = e % RX2;
+      const bool low = e / RX2 % 2 == 0;
+      const int row = low ? 1 : g.ny - j0 + 2, d = low ? RX2 : -RX2;   // R2 rows of j = -1, ny
+      if (low ? j0 != 0 : j0 + TY + 1 < g.ny) continue;
+      const int o = row * RX2 + x;
+      const T a0 = vel[c][o + d];
+      vel[c][o] = a0 - (vel[c][o + 2 * d] - a0);
+    }
+  };
+  // |S| of the own cell on plane k; the first and last planes also fill the ghost plane (odd about
+  // walls, periodic copy otherwise)
+  auto store_plane = [&](int k, T val) {
+    const int o = (j0 + ty) * g.nx + i0 + tx;
+    PlaneLoader<T>(nut, k, sxy).store(o, val);
+    if (k == 1) PlaneLoader<T>(nut, per ? nz + 1 : 0, sxy).store(o, per ? val : -val);
+    if (k == nz) PlaneLoader<T>(nut, per ? 0 : nz + 1, sxy).store(o, per ? val : -val);
+  };
+  // z weights (lower, centre, upper) of the unnormalised test filter: (1, 2, 1), the identity
+  // (0, 4, 0) for z-centred quantities on the first off-wall layers, 0 for w on the top wall face
+  auto zw = [&](int q, bool centred, int which) -> T {
+    if (!per && !centred && q == nz) return (T)0;
+    if (!per && centred && (q == 1 || q == nz)) return which == 1 ? (T)4 : (T)0;
+    return which == 1 ? (T)2 : (T)1;
+  };
+  // planes of the march: filter inputs on pstart..pend, velocity from qstart
+  const int pstart = per ? kb - 1 : max(kb - 1, 1);
+  const int pend = per ? ke + 1 : min(ke + 1, nz);
+  const bool from_wall = !per && pstart == 1;
+  const int qstart = from_wall ? 1 : pstart - 1;
+  const int qlast = per ? pend + 1 : min(pend + 1, nz);   // last velocity plane read
+  auto inside = [&]() { return i0 + tx < g.nx && j0 + ty < g.ny; };
+  T fwb = (T)0, fwt = (T)0;   // x-y filtered w of planes 1 and nz - 1 at the own cell (z walls)
+  // ducts: filtered V of the first and last rows (z sums of its own; fv: plane p, fvk: plane k)
+  T V1 = (T)0, V2 = (T)0, fv = (T)0, fvk = (T)0;
+  auto yedge = [&]() { return YW && (j0 + ty == 0 || j0 + ty == g.ny - 1); };   // duct: first or last row
+  // reciprocal spacing (over 8) of the z difference between planes q - 1 and q: twice the cell's
+  // own value across a bottom wall with no-slip, nothing beyond the top wall (the march prepares it)
+  auto rz8 = [&](int q) -> T {
+    if (!per && q > nz) return (T)0;
+    return ((from_wall && q == 1) ? (T)0.25 : (T)0.125) * (T)ro_load(g.rdzc, phys(q - 1));
+  };
+  // planes next to the z walls: C is the point's march at plane q - 1, n plane q; lx, ly the lower
+  // edge terms of plane q - 1.  Edge on the bottom wall, wall model: the z difference of the edge
+  // above it; edge on the top wall, prepared in n.wx, n.wy: that of the edge below it, or twice
+  // the cell's own value (no-slip)
+  auto wall_edges = [&](int q, const Strain<T>& C, Strain<T>& n, T ex, T ey, T& lx, T& ly, T plw, bool mine) {
+    if (mine && q == 1) fwb = plw;
+    if (mine && q == nz - 1) fwt = plw;
+    if (wm && from_wall && q == 2) {
+      lx = ex - C.wx;
+      ly = ey - C.wy;
+    }
+    if (q == nz) {
+      const T r8 = (T)0.25 * (T)ro_load(g.rdzc, nz);
+      n.wx = wm ? ex - C.wx : -r8 * n.U;
+      n.wy = wm ? ey - C.wy : -r8 * n.V;
+    }
+  };
+  // ---- plane q at one point: filtered velocity of plane q - 1, strain and filter inputs of plane
+  // q - 1; x, y in R1 coordinates.  Beyond the top wall (q = nz + 1) the LDS plane is stale and all
+  // of it is multiplied by zero.  Straight-line code but for the planes next to the walls.
+  auto point = [&](int q, int x, int y, Strain<T>& C, T (&G1)[3], T (&G2)[3], bool mine) {
+    const int e = y * RX1 + x;
+    const int o = (y + 1) * RX2 + x + 1;
+    Strain<T> n;
+    const int jr = j0 - 1 + y;
+    const bool edge = YW && (jr == 0 || jr == g.ny - 1);
+    T pl[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      T nb[3][3], r[3];
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) nb[dy][dx] = vel[c][o + (dy - 1) * RX2 + dx - 1];
+      strain_inplane<T>(c, nb, rdx, rdy, n);
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) r[dy] = (T)2 * nb[dy][1] + (nb[dy][0] + nb[dy][2]);
+      if (YW && c != 1)
+        pl[c] = edge ? (T)4 * r[1] : (T)2 * r[1] + (r[0] + r[2]);
+      else
+        pl[c] = (T)2 * r[1] + (r[0] + r[2]);
+      if (YW && c == 1) {
+        if (mine) {
+          const T vr = (T)4 * (jr == 0 ? r[1] : r[0]);
+          fv = V1 + zw(q - 1, true, 2) * vr;
+          V1 = V2 + zw(q, true, 1) * vr;
+          V2 = zw(q + 1, true, 0) * vr;
+        }
+        if (jr >= g.ny - 1 || jr < 0) pl[c] = (T)0;   // v~ on and beyond the y walls
+      }
+      ut[c][e] = G1[c] + zw(q - 1, c < 2, 2) * pl[c];
+      G1[c] = G2[c] + zw(q, c < 2, 1) * pl[c];
+      G2[c] = zw(q + 1, c < 2, 0) * pl[c];
+    }
+    T lx = C.ex, ly = C.ey;
+    strain_edges<T>(C, n, rz8(q), n.ex, n.ey);
+    if (!per && (q <= 2 || q >= nz - 1)) wall_edges(q, C, n, n.ex, n.ey, lx, ly, pl[2], mine);
+    const T s[6] = {C.s11, C.s22, (C.w - C.wl) * (T)ro_load(g.rdzf, phys(q - 1)), C.s12, n.ex + lx, n.ey + ly};
+    const T sm_ = strain_norm<T>(s);
+    const T U = C.U, V = C.V, W = C.w + C.wl;
+    const T in[NQ] = {U * U, V * V, W * W, U * V, U * W, V * W,
+                      sm_ * s[0], sm_ * s[1], sm_ * s[2], sm_ * s[3], sm_ * s[4], sm_ * s[5]};
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+      Pack t;
+#pragma unroll
+      for (int b = 0; b < PN; ++b) t.x[b] = in[a * PN + b];
+      qb[a][e] = t;
+    }
+    if (mine && nut != nullptr && q - 1 >= kb && q - 1 <= ke && inside()) store_plane(q - 1, sm_);
+    n.wl = C.w;
+    C = n;
+  };
+  // x sums of the inputs at R1 point (x, y)
+  auto xsums = [&](int x, int y) {
+    const int e = y * RX1 + x;
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+      const Pack l = qb[a][e - 1], m = qb[a][e], r = qb[a][e + 1];
+      Pack t;
+#pragma unroll
+      for (int b = 0; b < PN; ++b) t.x[b] = (T)2 * m.x[b] + (l.x[b] + r.x[b]);
+      xb[a][y * TX + x - 1] = t;
+    }
+  };
+  // running sums of the z pass of the test filter over the thread's cell: S1 holds
+  // plane p's sum without its upper neighbour, S2 plane p + 1's lower-neighbour term
+  T S1[NQ] = {}, S2[NQ] = {};
+  // y sums of the inputs of plane p, folded into the z sums; F: the filtered inputs of plane p - 1
+  auto filter = [&](int p, T (&F)[NQ]) {
+    const T zu = zw(p - 1, true, 2), zc = zw(p, true, 1), zl = zw(p + 1, true, 0);
+    const T ws = yedge() ? (T)0 : (T)1, wc = yedge() ? (T)4 : (T)2;
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+      const Pack lo = xb[a][tid], m = xb[a][tid + TX], hi = xb[a][tid + 2 * TX];
+#pragma unroll
+      for (int b = 0; b < PN; ++b) {
+        const int c = a * PN + b;
+        const T q = YW ? wc * m.x[b] + ws * (lo.x[b] + hi.x[b]) : (T)2 * m.x[b] + (lo.x[b] + hi.x[b]);
+        F[c] = S1[c] + zu * q;
+        S1[c] = S2[c] + zc * q;
+        S2[c] = zl * q;
+      }
+    }
+  };
+  // ducts: the y ghost rows of u~ and w~ by the strain ghost rule (extrapolated with the wall
+  // model, odd with no-slip), from the completed rows next to them
+  auto fix_rows = [&]() {
+    for (int e = tid; e < N1; e += NT) {
+      const int jr = j0 - 1 + e / RX1;
+      if (jr != -1 && jr != g.ny) continue;
+      const int d = jr < 0 ? RX1 : -RX1;   // one row inward
+      for (int c = 0; c < 3; c += 2) {
+        const T a0 = ut[c][e + d];
+        ut[c][e] = wm ? a0 - (ut[c][e + 2 * d] - a0) : -a0;
+      }
+    }
+  };
+  // ---- output plane k from F, the test-filtered inputs of its cell (times 64, the products
+  // times 4 more), the strain march CT of the filtered velocity (times 64), its upper edge terms
+  // (ex, ey) and lower ones (lx, ly) of plane k
+  Strain<T> CT = {};
+  double hs = 0.0;   // plane sums of the cells (half_sums)
+  auto output = [&](int k, const T (&F)[NQ], T ex, T ey, T lx, T ly) {
+    const int pk = phys(k);
+    const T st[6] = {CT.s11, CT.s22, (CT.w - CT.wl) * (T)ro_load(g.rdzf, pk), CT.s12, ex + lx, ey + ly};
+    const bool wall_layer = !per && (k == 1 || k == nz);
+    // 3-D, 2-D or (duct corners) 1-D test filter: 4, 4^(2/3), 2^(2/3)
+    const T alpha2 = (wall_layer && yedge()) ? (T)1.5874010519681994
+                                           : ((wall_layer || yedge()) ? (T)2.5198420997897464 : (T)4);
+    const T am = (alpha2 * (T)0.015625) * strain_norm<T>(st);
+    T fv_ = CT.V, fw = CT.w + CT.wl;
+    if (!per && k == 1) fw = (T)4 * fwb;
+    if (!per && k == nz) fw = (T)4 * fwt;
+    if (YW && yedge()) fv_ = fvk;
+    const T q64 = (T)0.015625, gu = q64 * CT.U, gv = q64 * fv_, gw = q64 * fw;
+    const T Fa[6] = {CT.U, fv_, fw, CT.U, CT.U, fv_}, Fb[6] = {gu, gv, gw, gv, gw, gw};
+    double la = 0.0, lo = 0.0, ma = 0.0, mo = 0.0;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const T Lc = F[c] - Fa[c] * Fb[c], Mc = F[6 + c] - am * st[c];
+      const double L = (double)Lc, m = (double)Mc;
+      if (c < 3) {
+        la += L * m;
+        ma += m * m;
+      } else {
+        lo += L * m;
+        mo += m * m;
+      }
+    }
+    const double d2 = ro_load(g.delta2, pk) * (1.0 / 32.0);   // 2 Delta^2 / 64
+    const double lm = inside() ? (la + 2.0 * lo) * (d2 * (1.0 / 256.0)) : 0.0;
+    const double mm = inside() ? (ma + 2.0 * mo) * (d2 * d2) : 0.0;
+    hs = half_sums(lm, mm);
+  };
+  // sums of plane k to memory: called one iteration later, so that no store is young when the loads
+  // of a plane are waited for
+  auto put_sums = [&](int k) {
+    if (k < kb || k > ke) return;
+    if (YW) {
+      // x-line sums: a row of the tile is 32 lanes of one wave; partials [k][j][tile x]
+      const int jrow = j0 + ty;
+      if (tx % 16 == 0 && jrow < g.ny) part[(((int64_t)(k - 1) * g.ny + jrow) * gdx + bid.x) * 2 + tx / 16] = hs;
+      return;
+    }
+    // the waves' partials go out per plane and are summed over (tile, wave) in a fixed order by
+    // the plane reduction
+    const double lm = lane_f64(hs, 0) + lane_f64(hs, 32);
+    const double mm = lane_f64(hs, 16) + lane_f64(hs, 48);
+    if (tid % 64 == 0) {
+      double* pk2 = part + (((int64_t)(k - 1) * ntile + tile) * WV + __builtin_amdgcn_readfirstlane(tid / 64)) * 2;
+      pk2[0] = lm;
+      pk2[1] = mm;
+    }
+  };
+  // start of an iteration: plane q has arrived
+  auto arrive = [&](int q) {
+    if constexpr (DIRECT)
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the thread's loads to LDS
+    else if (q <= qlast)
+      commit();
+    lds_barrier();
+    if (ywall_block && q <= qlast) {
+      extrapolate_rows();
+      lds_barrier();
+    }
+    if (!DIRECT && q < qlast) fetch(q + 1);
+  };
+  fetch(qstart);
+  // ---- march.  Threads exchange data through LDS only (the stored |S| and partial sums are read
+  // by later launches): the barriers leave global loads in flight.
+  Strain<T> C = {};
+  T G1[3] = {}, G2[3] = {};
+  if (tid < NHALO)
+    for (int a = 0; a < Strain<T>::N + 6; ++a) hst[a][tid] = (T)0;
+#pragma unroll 1
+  for (int q = qstart; q <= pend + 1; ++q) {
+    const int p = q - 1, k = q - 2;
+    if constexpr (YW || per) {
+      // LDS addresses from here are worked out anew on each plane: where registers would hold them between
+      // planes, some are spilled, and a reload waits for the loads and stores under way
+      asm volatile("" : "+v"(tid));
+      tx = tid % TX;
+      ty = tid / TX;
+    }
+    arrive(q);
+    put_sums(q - 3);
+    point(q, tx + 1, ty + 1, C, G1, G2, true);
+    // the thread's halo-1 point (R1 coordinates), if it has one: the rows below and above the tile, then
+    // the columns beside it
+    const int hc = tid - NROW;
+    const int hx = hc < 0 ? tx + 1 : (hc < RY1 ? 0 : RX1 - 1), hy = hc < 0 ? (tid < TX ? 0 : RY1 - 1) : hc % RY1;
+    if (tid < NHALO) {
+      struct {
+        Strain<T> m;
+        T G1[3], G2[3];
+      } H;
+      T h[Strain<T>::N + 6];
+#pragma unroll
+      for (int a = 0; a < Strain<T>::N + 6; ++a) h[a] = hst[a][tid];
+      static_assert(sizeof(H) == sizeof(h), "all of it T");
+      __builtin_memcpy(&H, h, sizeof(h));
+      point(q, hx, hy, H.m, H.G1, H.G2, false);
+      __builtin_memcpy(h, &H, sizeof(h));
+#pragma unroll
+      for (int a = 0; a < Strain<T>::N + 6; ++a) hst[a][tid] = h[a];
+    }
+    lds_barrier();
+    if (DIRECT && q < qlast) fetch(q + 1);
+    if (p < pstart) continue;
+    xsums(tx + 1, ty + 1);
+    if (tid < NROW) xsums(hx, hy);
+    if (YW) fix_rows();
+    lds_barrier();
+    // filtered velocity of plane p at the own cell, and the upper edge terms of plane k
+    Strain<T> n;
+    T ex, ey;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      T nb[3][3];
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) nb[dy][dx] = ut[c][(ty + dy) * RX1 + tx + dx];
+      strain_inplane<T>(c, nb, rdx, rdy, n);
+    }
+    strain_edges<T>(CT, n, rz8(p), ex, ey);
+    T lx = CT.ex, ly = CT.ey;
+    if (!per && (p <= 2 || p == nz)) wall_edges(p, CT, n, ex, ey, lx, ly, (T)0, false);
+    T F[NQ];
+    filter(p, F);
+    output(k, F, ex, ey, lx, ly);
+    n.wl = CT.w;
+    n.ex = ex;
+    n.ey = ey;
+    CT = n;
+    if (YW) fvk = fv;
+  }
+  put_sums(pend - 1);
+  if (!per && ke == nz) {   // the z pass is the identity on the top layer
+    output(nz, S1, CT.wx, CT.wy, CT.ex, CT.ey);
+    put_sums(nz);
+  }
+}
+
+template <typename T, bool YW, int ZBC>
+__global__ void __launch_bounds__(fused::Tile<T>::NT, fused::Tile<T>::WEU) k_dsm_fused(GridP g, const T* u, const T* v,
+                                                                                    const T* w, T* nut, double* part,
+                                                                                    int kc, const int* gate) {
+  dsm_fused_body<T, YW, ZBC>(xcd_tile(blockIdx, gridDim), gridDim.x, gridDim.y, g, u, v, w, nut, part, kc, gate);
+}
+
+// ---------------------------------------------------------------- FP32 with walls or Crank-Nicolson
+// The same model with every value rounded where an FP32 run has always rounded it: the four edges of a cell
+// apart, 15 inputs (the centre velocities among them) through the 9-point filter term by term.  L is a
+// difference of nearly equal FP32 values, so either kernel's c_s is off by some 1e-7 (between walls up to 5e-4),
+// and the pressure of an FP32 run answers the last bits of the eddy viscosity: by 3e-4 of itself in a channel
+// (1024x512x256) and 3e-5 in a 256^3 box with Crank-Nicolson in all directions, as much as its distance from a
+// 64-bit solution, but by 1e-6 in periodic boxes with explicit viscous terms at any size.  The kernel above is faster
+// (3217 -> 2223 us on that channel) and not closer (2.9e-4 against 2.2e-4), so in FP32 only the last take it.
+//   LDS: velocity of planes p, p + 1 on the tile + 2 halo (strain ghosts substituted), the 15 filter inputs (u_i,
+//        u_i u_j, |S| S_ij at cell centres) of plane p on the tile + 1 halo in pairs, the test-filtered
+//        staggered velocity of two planes on the tile + 1 halo.
+//   Registers: the z pass of the test filter as running sums over the thread's cell; the upper z-edge terms of the
+//        off-diagonal strain and w of the previous plane at the thread's points, the lower terms of the plane
+//        above.
+// The stage of plane p forms the filter inputs of plane p from velocity planes p, p + 1 and completes the
+// filtered velocity of plane p - 1; then the cell values of plane p - 1 are final.
+namespace fused32 {
+constexpr int TX = 32;
+constexpr int NQ = 15;   // filter inputs per cell
+template <typename T, bool YW>
+struct Tile {
+  static constexpr int TY = dsm_tile_rows(false), NT = TX * TY, WV = NT / 64;
   static constexpr int RX2 = TX + 4, RY2 = TY + 4, N2 = RX2 * RY2;  // halo 2
   static constexpr int RX1 = TX + 2, RY1 = TY + 2, N1 = RX1 * RY1;  // halo 1
   static constexpr int NHALO = 2 * (RX1 + TY);                       // halo-1 points around the tile
-  static constexpr int MINB = sizeof(T) == 8 ? (YW ? 2 : 1) : 3;     // blocks per CU
 };
-}  // namespace fused
+}  // namespace fused32
 
 // Upper z-edge terms at a cell of plane k: (du/dz + dw/dx) / 2 on the x-z edges of the cell's
 // two x faces (fa: the face of u_i, fb: of u_{i-1}), (dv/dz + dw/dy) / 2 on the y-z edges of
@@ -440,44 +960,18 @@ __device__ inline void strain_zm(const Acc& A, int o, int sy, T rdx, T rdy, T rd
   s[5] = q * (E.ga + E.gb + P.ga + P.gb);
 }
 
-// x of another lane of the same row of 16 lanes, by a DPP lane pattern
-template <int CTRL>
-__device__ inline double dpp_f64(double x) {
-  const int lo = __double2loint(x), hi = __double2hiint(x);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, false));
-}
-// sum over each row of 16 lanes, a 4-level tree (partners at lane distance 1 and 2 in a quad,
-// then the mirrored half-row and row): every lane of a row holds the same bits
-__device__ inline double row_sum(double x) {
-  x = x + dpp_f64<0xB1>(x);    // quad permutation 1 0 3 2
-  x = x + dpp_f64<0x4E>(x);    // quad permutation 2 3 0 1
-  x = x + dpp_f64<0x141>(x);   // half-row mirror
-  x = x + dpp_f64<0x140>(x);   // row mirror
-  return x;
-}
-// lane L's value of x, uniform across the wave
-__device__ inline double lane_f64(double x, int L) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), L),
-                          __builtin_amdgcn_readlane(__double2loint(x), L));
-}
 template <typename T>
-__device__ inline T strain_norm(const T s[6]) {
+__device__ inline T strain_norm32(const T s[6]) {
   return sqrt((T)2 * (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) + (T)4 * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]));
 }
 
-// YW (ducts, walls in y too): the y pass of the test filter is the identity on the first and
-// last rows for y-centred quantities (u, w and the 15 cell quantities), v~ vanishes on and
-// beyond the y wall faces, the y ghost rows of u~ and w~ follow the strain ghost rule, alpha^2
-// counts the filter's dimensions per cell, and the partial sums are per x line (one per row
-// of each wave: 32 lanes) instead of per wave.
-template <typename T, bool YW = false, int ZBC = -1>
-__device__ __forceinline__ void dsm_fused_body(dim3 bid, int gdx, int gdy, GridP g, const T* __restrict__ u,
+template <typename T, bool YW>
+__device__ __forceinline__ void dsm_fused32_body(dim3 bid, int gdx, int gdy, GridP g, const T* __restrict__ u,
                                                const T* __restrict__ v, const T* __restrict__ w,
                                                T* __restrict__ nut, double* __restrict__ part, int kc,
                                                const int* __restrict__ gate) {
-  using TL = fused::Tile<T, YW>;
-  constexpr int TX = fused::TX, TY = TL::TY, NT = TL::NT, WV = TL::WV, NQ = fused::NQ;
+  using TL = fused32::Tile<T, YW>;
+  constexpr int TX = fused32::TX, TY = TL::TY, NT = TL::NT, WV = TL::WV, NQ = fused32::NQ;
   constexpr int RX2 = TL::RX2, N2 = TL::N2, RX1 = TL::RX1, RY1 = TL::RY1, N1 = TL::N1, NHALO = TL::NHALO;
   if (gate != nullptr && gate[0] == 0) return;   // learned closure: no point fell back
   constexpr int NL = (N2 + NT - 1) / NT;          // halo-2 points per thread (loads)
@@ -491,7 +985,7 @@ __device__ __forceinline__ void dsm_fused_body(dim3 bid, int gdx, int gdy, GridP
   const int nz = g.nz;
   const int kb = 1 + bid.z * kc;
   const int ke = min(nz, kb + kc - 1);
-  const int zbc = ZBC < 0 ? g.zbc : ZBC;   // ZBC >= 0: the z boundary fixed at compile time
+  const int zbc = g.zbc;
   const bool per = zbc == LES_ZBC_PERIODIC;
   const bool wm = zbc == LES_ZBC_WALLMODEL;
   const int ntile = gdx * gdy;
@@ -669,7 +1163,7 @@ __device__ __forceinline__ void dsm_fused_body(dim3 bid, int gdx, int gdy, GridP
       const ZEdges<T> E = zedges<T>(A, o, RX2, rdx, rdy, rdzc);
       T s[6];
       strain_zm<T>(A, o, RX2, rdx, rdy, rdzf, P, E, s);
-      const T sm_ = strain_norm<T>(s);
+      const T sm_ = strain_norm32<T>(s);
       const int e = (y - 1) * RX1 + x - 1;
       const T uc = (T)0.5 * (A(0, 0, o) + A(0, 0, o - 1));
       const T vc = (T)0.5 * (A(1, 0, o) + A(1, 0, o - RX2));
@@ -743,7 +1237,7 @@ __device__ __forceinline__ void dsm_fused_body(dim3 bid, int gdx, int gdy, GridP
         PT = E;
     }
     if (i < g.nx && j < g.ny) {
-      const T stm = strain_norm<T>(st);
+      const T stm = strain_norm32<T>(st);
       const bool wall_layer = !per && (k == 1 || k == nz);
       const bool wall_row = YW && (j == 0 || j == g.ny - 1);
       // 3-D, 2-D or (duct corners) 1-D test filter: 4, 4^(2/3), 2^(2/3)
@@ -877,10 +1371,10 @@ __device__ __forceinline__ void dsm_fused_body(dim3 bid, int gdx, int gdy, GridP
   if (!per && ke == nz) output(nz, S1);   // the z pass is the identity on the top layer
 }
 
-template <typename T, bool YW = false, int ZBC = -1>
-__global__ void __launch_bounds__((fused::Tile<T, YW>::NT), (fused::Tile<T, YW>::MINB)) k_dsm_fused(GridP g, const T* u, const T* v, const T* w, T* nut, double* part,
-                                                   int kc, const int* gate) {
-  dsm_fused_body<T, YW, ZBC>(xcd_tile(blockIdx, gridDim), gridDim.x, gridDim.y, g, u, v, w, nut, part, kc, gate);
+template <typename T, bool YW>
+__global__ void __launch_bounds__((fused32::Tile<T, YW>::NT), dsm_blocks_per_cu(false))
+    k_dsm_fused32(GridP g, const T* u, const T* v, const T* w, T* nut, double* part, int kc, const int* gate) {
+  dsm_fused32_body<T, YW>(xcd_tile(blockIdx, gridDim), gridDim.x, gridDim.y, g, u, v, w, nut, part, kc, gate);
 }
 
 // Ducts: c_s per x line (j, k) from the tile partials [k][j][tile x], summed in tile order,
@@ -914,14 +1408,14 @@ __global__ void __launch_bounds__(256) k_nut_lines(GridP g, T* nut, const double
   nut[c] = (T)((double)nut[c] * cs[(int64_t)(kk - 1) * g.ny + j]);
 }
 
-// Batched dynamic model (and its plane / volume reduction) over all boxes of a batch.
+// Batched dynamic model (and its plane / volume reduction) over all boxes of a batch (periodic boxes).
 template <typename T>
-__global__ void __launch_bounds__(fused::Tile<T>::NT, fused::Tile<T>::MINB) kb_dsm_fused(BatchMap m) {
+__global__ void __launch_bounds__(fused::Tile<T>::NT, fused::Tile<T>::WEU) kb_dsm_fused(BatchMap m) {
   int box;
   const dim3 bid = batch_bid(m, BK_DSM, blockIdx.x, box);
   const BoxDesc& d = m.desc[box];
-  dsm_fused_body<T>(bid, d.gdim[BK_DSM][0], d.gdim[BK_DSM][1], d.g, (const T*)d.u, (const T*)d.v, (const T*)d.w,
-                    (T*)d.nut, d.dsm_part, d.kc, nullptr);
+  dsm_fused_body<T, false, LES_ZBC_PERIODIC>(bid, d.gdim[BK_DSM][0], d.gdim[BK_DSM][1], d.g, (const T*)d.u, (const T*)d.v,
+                                             (const T*)d.w, (T*)d.nut, d.dsm_part, d.kc, nullptr);
 }
 
 template <typename T>
@@ -1408,9 +1902,10 @@ void launch_eddy_viscosity(Ctx& c) {
     T* dsm_nut = learned ? nullptr : (T*)c.nut;
     const int kc = c.dsm_kc;
     using TL = fused::Tile<T>;
-    using TLY = fused::Tile<T, true>;   // ducts
-    const int dty = g.ywall ? TLY::TY : TL::TY;
-    dim3 grid((g.nx + fused::TX - 1) / fused::TX, (g.ny + dty - 1) / dty, (g.nz + kc - 1) / kc);
+    const dim3 grid((g.nx + fused::TX - 1) / fused::TX, (g.ny + TL::TY - 1) / TL::TY, (g.nz + kc - 1) / kc);
+    // FP32 keeps its rounding but in periodic boxes with explicit viscous terms (k_dsm_fused32, 32 x 8 threads)
+    const bool rows32 = sizeof(T) == 4 && (g.zbc != LES_ZBC_PERIODIC || c.cfg.implicit_z != LES_VISC_EXPLICIT);
+    const dim3 block = rows32 ? dim3(fused32::TX, TL::NT / fused32::TX) : dim3(TL::NT);
     if (learned) {
       MlpNorm nm;
       for (int a = 0; a < 7; ++a) {
@@ -1443,12 +1938,14 @@ void launch_eddy_viscosity(Ctx& c) {
     }
     if (g.ywall) {
       // ducts: coefficients along x lines
-      // FP64 with the wall model: the z boundary fixed at compile time (no spill; 225 -> 215 us
-      // on the 512x80x80 duct)
-      auto kfy = k_dsm_fused<T, true>;
-      if constexpr (sizeof(T) == 8)
-        if (g.zbc == LES_ZBC_WALLMODEL) kfy = k_dsm_fused<T, true, LES_ZBC_WALLMODEL>;
-      LES_LAUNCH(c, "dsm_fused", 4 * pts * sizeof(T), kfy, grid, dim3(fused::TX, TLY::TY), 0, g,
+      auto kfy = [&] {
+        if constexpr (sizeof(T) == 4)
+          return k_dsm_fused32<T, true>;
+        else
+          return g.zbc == LES_ZBC_WALLMODEL ? k_dsm_fused<T, true, LES_ZBC_WALLMODEL>
+                                            : k_dsm_fused<T, true, LES_ZBC_NOSLIP>;
+      }();
+      LES_LAUNCH(c, "dsm_fused", 4 * pts * sizeof(T), kfy, grid, block, 0, g,
                  (const T*)c.u, (const T*)c.v, (const T*)c.w, dsm_nut, c.t.dsm_part, kc, gate);
       const int nl = g.nz * g.ny;
       LES_LAUNCH(c, "dsm_reduce", 0, k_dsm_reduce_lines, dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, g,
@@ -1459,15 +1956,14 @@ void launch_eddy_viscosity(Ctx& c) {
                    0, g, (T*)c.nut, (const double*)c.t.cs);
       }
     } else {
-      // FP64 channels with walls: the z boundary fixed at compile time (the wall-model build
-      // needs 238 VGPRs instead of 255 and ran 674 -> 603 us on 512x256x128; in FP32, and
-      // for periodic z, where the fixed builds measured slower, it stays a run-time value)
-      auto kf = k_dsm_fused<T, false>;
-      if constexpr (sizeof(T) == 8) {
-        if (g.zbc == LES_ZBC_WALLMODEL) kf = k_dsm_fused<T, false, LES_ZBC_WALLMODEL>;
+      auto kf = k_dsm_fused<T, false, LES_ZBC_PERIODIC>;
+      if constexpr (sizeof(T) == 4) {
+        if (rows32) kf = k_dsm_fused32<T, false>;
+      } else {
         if (g.zbc == LES_ZBC_NOSLIP) kf = k_dsm_fused<T, false, LES_ZBC_NOSLIP>;
+        if (g.zbc == LES_ZBC_WALLMODEL) kf = k_dsm_fused<T, false, LES_ZBC_WALLMODEL>;
       }
-      LES_LAUNCH(c, "dsm_fused", 4 * pts * sizeof(T), kf, grid, dim3(fused::TX, TL::TY), 0, g,
+      LES_LAUNCH(c, "dsm_fused", 4 * pts * sizeof(T), kf, grid, block, 0, g,
                  (const T*)c.u, (const T*)c.v, (const T*)c.w, dsm_nut, c.t.dsm_part, kc, gate);
       const int ntile = (int)(grid.x * grid.y) * TL::WV;
       LES_LAUNCH(c, "dsm_reduce", 0, k_dsm_reduce<T>, dim3(g.nz), dim3(256), 0, g, c.t.dsm_part, ntile, c.t.cs,
@@ -1486,7 +1982,7 @@ template <typename T>
 void batch_eddy_viscosity(hipStream_t st, const BatchMap& m, const int* totals, int any_dsm, int any_smag) {
   if (any_smag) hipLaunchKernelGGL(kb_strain_mag<T>, dim3(totals[BK_POINT]), dim3(32, 8), 0, st, m);
   if (any_dsm) {
-    hipLaunchKernelGGL(kb_dsm_fused<T>, dim3(totals[BK_DSM]), dim3(fused::TX, fused::Tile<T>::TY), 0, st, m);
+    hipLaunchKernelGGL(kb_dsm_fused<T>, dim3(totals[BK_DSM]), dim3(fused::Tile<T>::NT), 0, st, m);
     hipLaunchKernelGGL(kb_dsm_reduce<T>, dim3(totals[BK_DSMRED]), dim3(256), 0, st, m);
   }
 }
