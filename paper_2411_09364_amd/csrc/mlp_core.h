@@ -68,12 +68,18 @@ struct alignas(16) Weights {
   float b3;
 };
 
-__device__ void load_weights(const float* __restrict__ P, Weights& W, int tid, int nthr) {
+// With w2t, W2 is stored transposed as well (rows padded alike).
+__device__ void load_weights(const float* __restrict__ P, Weights& W, int tid, int nthr,
+                             unsigned short* w2t = nullptr) {
   for (int e = tid; e < H * FP; e += nthr) {
     const int r = e / FP, f = e % FP;
     W.w1[e] = f < F ? f2bf(P[P_W1 + r * F + f]) : (unsigned short)0;
   }
-  for (int e = tid; e < H * H; e += nthr) W.w2[(e / H) * LD2 + e % H] = f2bf(P[P_W2 + e]);
+  for (int e = tid; e < H * H; e += nthr) {
+    const unsigned short w = f2bf(P[P_W2 + e]);
+    W.w2[(e / H) * LD2 + e % H] = w;
+    if (w2t) w2t[(e % H) * LD2 + e / H] = w;
+  }
   for (int e = tid; e < H; e += nthr) {
     W.b1[e] = P[P_B1 + e];
     W.b2[e] = P[P_B2 + e];
