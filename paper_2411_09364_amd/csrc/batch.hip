@@ -33,7 +33,7 @@ struct les_batch {
   BoxDesc* ddesc = nullptr;
   int* dprefix = nullptr;
   int totals[BK_NKIND] = {0};
-  size_t sh_x = 0, sh_y = 0, sh_z = 0;
+  FftLaunch fft[3] = {};   // block and LDS sizes of the x, y and z transforms
   bool dirty = true;
   int tune_kc = 0;   // 0: def_kc; else planes per dynamic-model chunk
   int def_kc = 8;    // default chunk (at most a box's planes)
@@ -60,12 +60,6 @@ void drop_graph(les_batch* b) {
   b->graph = nullptr;
 }
 
-int pow2_at_most(int v) {
-  int p = 1;
-  while (p * 2 <= v) p *= 2;
-  return p;
-}
-
 // Descriptors and prefix tables of the current tuning; uploaded into the workspace tail.
 les_status prepare(les_batch* b) {
   if (!b->dirty) return LES_OK;
@@ -75,7 +69,7 @@ les_status prepare(les_batch* b) {
   const size_t E = b->prec == LES_MIXED ? 4 : 8;
   b->hdesc.assign(b->nbox, BoxDesc{});
   b->hprefix.assign((size_t)BK_NKIND * (b->nbox + 1), 0);
-  b->sh_x = b->sh_y = b->sh_z = 0;
+  for (FftLaunch& f : b->fft) f = FftLaunch{};
   for (int i = 0; i < b->nbox; ++i) {
     Ctx& c = b->box[i]->c;
     BoxDesc& d = b->hdesc[i];
@@ -111,9 +105,10 @@ les_status prepare(les_batch* b) {
     d.px = make_plan(nx);
     d.py = make_plan(ny);
     d.pz = make_plan(nz);
-    d.pbx = fft_pairs_per_block(nx);
-    d.ly = b->tune_l ? std::min(b->tune_l, pow2_at_most(std::max(1, 2048 / ny))) : fft_lines_per_block(ny);
-    d.lz = b->tune_l ? std::min(b->tune_l, pow2_at_most(std::max(1, 2048 / nz))) : fft_lines_per_block(nz);
+    const FftLaunch fl[3] = {fft_rows(nx, 2 * E), fft_lines(ny, 2 * E, b->tune_l), fft_lines(nz, 2 * E, b->tune_l)};
+    d.pbx = fl[0].per;
+    d.ly = fl[1].per;
+    d.lz = fl[2].per;
     d.kc = std::min(b->tune_kc ? b->tune_kc : b->def_kc, nz);
     d.pkc = c.pred_kc;
     d.sgs = c.cfg.sgs;
@@ -131,9 +126,10 @@ les_status prepare(les_batch* b) {
     set(BK_DSMRED, nz, 1, 1);
     set(BK_CFL, 64, 1, 1);
     set(BK_PRED, (nx + 31) / 32, (ny + 7) / 8, (nz + d.pkc - 1) / d.pkc);
-    b->sh_x = std::max(b->sh_x, 2 * (size_t)d.pbx * nx * 2 * E);
-    b->sh_y = std::max(b->sh_y, 2 * (size_t)d.ly * (ny + 1) * 2 * E);
-    b->sh_z = std::max(b->sh_z, 2 * (size_t)d.lz * (nz + 1) * 2 * E);
+    for (int a = 0; a < 3; ++a) {
+      b->fft[a].nt = std::max(b->fft[a].nt, fl[a].nt);
+      b->fft[a].sh = std::max(b->fft[a].sh, fl[a].sh);
+    }
   }
   for (int k = 0; k < BK_NKIND; ++k) {
     int* pre = &b->hprefix[(size_t)k * (b->nbox + 1)];
@@ -164,7 +160,7 @@ template <typename T>
 void substep_batch(les_batch* b, int stage) {
   const BatchMap m = map_of(b);
   batch_predictor<T>(b->stream, m, b->totals[BK_PRED], stage);
-  batch_poisson<T>(b->stream, m, b->totals, b->sh_x, b->sh_y, b->sh_z, stage);
+  batch_poisson<T>(b->stream, m, b->totals, b->fft, stage);
   batch_correct<T>(b->stream, m, b->totals[BK_POINT], stage);
   batch_eddy_viscosity<T>(b->stream, m, b->totals, b->sgs == LES_SGS_DSM, b->sgs == LES_SGS_SMAG);
 }

@@ -198,11 +198,11 @@ __device__ inline int wrap_p(int i, int n) { return i + 1 == n ? 0 : i + 1; }
 __host__ __device__ inline int factor_modes(const GridP& g) { return g.ywall ? g.ny : g.ny / 2 + 1; }
 __device__ inline int wrap_m(int i, int n) { return i == 0 ? n - 1 : i - 1; }
 
-// Radix plan of an LDS Stockham FFT (radix 3 first, then 4s, then a 2).
+// Passes of an LDS FFT: np >= 2, pass i joins the stages of radix pass[i] / 10 and pass[i] % 10.
 struct FftPlan {
   int n;
-  int nst;
-  int rad[16];
+  int np;
+  int pass[4];
 };
 FftPlan make_plan(int n);
 
@@ -427,13 +427,18 @@ template <typename T> void batch_predictor(hipStream_t st, const BatchMap& m, in
 template <typename T> void batch_correct(hipStream_t st, const BatchMap& m, int total, int stage);
 template <typename T> void batch_dt(hipStream_t st, const BatchMap& m, int total_cfl, int nbox, double cfl);
 void batch_set_dt(hipStream_t st, const BatchMap& m, int nbox, double dt);
+struct FftLaunch {
+  int per;     // row pairs or lines per block
+  int nt;      // threads per block
+  size_t sh;   // dynamic LDS bytes
+};
+// launches f[0] along x, f[1] along y, f[2] along z
 template <typename T>
-void batch_poisson(hipStream_t st, const BatchMap& m, const int* totals, size_t sh_x, size_t sh_y, size_t sh_z,
-                   int stage);
+void batch_poisson(hipStream_t st, const BatchMap& m, const int* totals, const FftLaunch* f, int stage);
 template <typename T>
 void batch_eddy_viscosity(hipStream_t st, const BatchMap& m, const int* totals, int any_dsm, int any_smag);
-int fft_pairs_per_block(int nx);
-int fft_lines_per_block(int n);
+FftLaunch fft_rows(int n, size_t esz);
+FftLaunch fft_lines(int n, size_t esz, int want);   // want: lines per block at most, 0 for the default
 
 }  // namespace les
 

@@ -4,14 +4,15 @@
 //   k_rfftx      f = D u* / (gamma dt) (or a given field) on two neighbouring x-rows,
 //                packed as one complex row, Stockham FFT in LDS, split into the two
 //                half spectra l = 0..nx/2; also the flow-rate partial sums of u*.
-//   k_fft_lines  complex FFT along y (or z) for tiles of consecutive l, in LDS.
-//   k_thomas     FP64 Thomas solve along z for every (l, m) column, staged through LDS;
-//                the singular (0, 0) column is pinned and mean-corrected.
-//   k_fftz_solve periodic z: forward FFT along z, division by the eigenvalue sum, inverse.
+//   k_fft_lines  complex FFT along y for tiles of consecutive l, from global memory into
+//                registers, through LDS once (twice) and back; or along a periodic z the
+//                forward FFT, the division by the eigenvalue sum and the inverse.
+//   k_thomas_scan  FP64 solve along z for every (l, m) column; the singular (0, 0) column is
+//                pinned and mean-corrected.
 //   k_irfftx     Hermitian reconstruction of two rows, inverse FFT, real and imaginary
 //                parts back to the two rows of phi.
 //
-// Spectrum layout: complex [nz][ny][nx/2+1] (l fastest), interior planes only.
+// Spectrum layout: complex [nz][ny][nxp] (l fastest, nxp >= nx/2+1), interior planes only.
 // Normalisation: forward transforms unscaled; the solve multiplies by 1/(nx ny [nz]) so
 // the inverse transforms are plain sums.
 #include "les_internal.h"
@@ -21,227 +22,268 @@
 namespace les {
 
 template <typename R>
-struct cpx {
+struct alignas(2 * sizeof(R)) cpx {
   R x, y;
 };
 
+// Passes of an LDS Stockham FFT.  The stages (radix 5, then 3, then 4s, then a 2; a sub-transform
+// of Ns points grows by the radix each stage) run two at a time: a thread takes the R1 R2 points
+// that both stages of a pair connect, so that a transform of up to 320 points goes through LDS
+// once, between its two passes, and one of up to 1024 points twice; the first pass of the strided
+// lines loads from global memory and the last one stores there.  Every stage's arithmetic is that
+// of the stage alone.  Bound by memory: with a stage per LDS pass (and the index divisions of
+// each butterfly) the y transforms of 512 x 256 x 128 in FP64 took 81 and 76 us, now 52 and 48
+// (271 MB moved, 5.1 and 5.6 TB/s), those of 1024 x 512 x 256 in FP32 553 and 467, now 255 (4.2
+// TB/s, what a large copy reaches).
 FftPlan make_plan(int n) {
   FftPlan p{};
   p.n = n;
-  int m = n;
-  int s = 0;
+  int rad[16], s = 0, m = n;
   if (m % 5 == 0) {
-    p.rad[s++] = 5;
+    rad[s++] = 5;
     m /= 5;
   }
   if (m % 3 == 0) {
-    p.rad[s++] = 3;
+    rad[s++] = 3;
     m /= 3;
   }
   while (m % 4 == 0) {
-    p.rad[s++] = 4;
+    rad[s++] = 4;
     m /= 4;
   }
   while (m % 2 == 0) {
-    p.rad[s++] = 2;
+    rad[s++] = 2;
     m /= 2;
   }
-  p.nst = s;
+  // pairs from the front, but of three stages, or of two that make 16 points or fewer, the first
+  // stands alone when the groups are smaller and more for it (32 = 4 x (4 2), not (4 4) x 2)
+  int i = 0;
+  if ((s == 3 && rad[1] * rad[2] < rad[0] * rad[1]) || (s == 2 && n <= 20)) p.pass[p.np++] = 10 * rad[i++] + 1;
+  for (; i < s; i += 2) p.pass[p.np++] = 10 * rad[i] + (i + 1 < s ? rad[i + 1] : 1);
+  // a last pass of one point per thread where the first already holds the whole transform
+  if (p.np == 1) p.pass[p.np++] = 11;
   return p;
 }
 
-// Stockham autosort FFT (sub-transform size Ns grows by the radix each stage).  src and
-// dst are ping-pong LDS buffers of one transform; `lane` and `team` split the butterflies
-// of a stage among the team's threads.  DIR = -1 forward (exp(-2 pi i q/N)), +1 inverse.
-// tw holds (cos, sin)(2 pi q/N), q = 0..N-1.  Each radix has its own body so that the
-// butterfly operands stay in registers.
+// Threads of one transform (a team): the power of two that leaves every thread 16 points at
+// most, or one group of the first pass; the later passes (16 points or fewer a group) then have
+// at most ceil(16 / (R1 R2)) groups a thread.
+static int fft_team(int n) {
+  const FftPlan p = make_plan(n);
+  const int need = std::max((n + 15) / 16, n / (p.pass[0] / 10 * (p.pass[0] % 10)));
+  int t = 1;
+  while (t < need) t *= 2;
+  return t;
+}
+
+// Sums of two products are written with their fused multiply-adds, one product rounded and
+// the other not: which one the compiler would fuse changes with the code around them, and with
+// it the last bits of every transform.
+__device__ inline float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// a (c + i s)
+template <typename R>
+__device__ inline cpx<R> turn(cpx<R> a, R c, R s) {
+  return {fmadd(a.x, c, -(a.y * s)), fmadd(a.y, c, a.x * s)};
+}
+
+// DIR = -1 forward (exp(-2 pi i q/N)), +1 inverse.  tw holds (cos, sin)(2 pi q/N), q = 0..N-1.
 template <typename R, int DIR>
 __device__ inline cpx<R> twiddle(cpx<R> a, const R* __restrict__ tw, int qq) {
-  const R c = tw[2 * qq], sn = (R)DIR * tw[2 * qq + 1];
-  return {a.x * c - a.y * sn, a.x * sn + a.y * c};
+  return turn(a, tw[2 * qq], (R)DIR * tw[2 * qq + 1]);
 }
 
-template <typename R, int DIR>
-__device__ inline void stage2(const cpx<R>* src, cpx<R>* dst, int N, int Ns, const R* tw, int lane, int team) {
-  const int nb = N / 2, ts = N / (Ns * 2);
-  for (int b = lane; b < nb; b += team) {
-    const int k = b % Ns;
-    const cpx<R> v0 = src[b];
-    const cpx<R> v1 = twiddle<R, DIR>(src[b + nb], tw, k * ts);
-    const int o = (b / Ns) * Ns * 2 + k;
-    dst[o] = {v0.x + v1.x, v0.y + v1.y};
-    dst[o + Ns] = {v0.x - v1.x, v0.y - v1.y};
-  }
-}
-
-template <typename R, int DIR>
-__device__ inline void stage4(const cpx<R>* src, cpx<R>* dst, int N, int Ns, const R* tw, int lane, int team) {
-  const int nb = N / 4, ts = N / (Ns * 4);
-  for (int b = lane; b < nb; b += team) {
-    const int k = b % Ns;
-    const cpx<R> v0 = src[b];
-    const cpx<R> v1 = twiddle<R, DIR>(src[b + nb], tw, k * ts);
-    const cpx<R> v2 = twiddle<R, DIR>(src[b + 2 * nb], tw, 2 * k * ts);
-    const cpx<R> v3 = twiddle<R, DIR>(src[b + 3 * nb], tw, 3 * k * ts);
+// butterfly of radix RAD on v[0], v[S], .., in place
+template <typename R, int DIR, int RAD, int S>
+__device__ __forceinline__ void butterfly(cpx<R>* v) {
+  if constexpr (RAD == 2) {
+    const cpx<R> v0 = v[0], v1 = v[S];
+    v[0] = {v0.x + v1.x, v0.y + v1.y};
+    v[S] = {v0.x - v1.x, v0.y - v1.y};
+  } else if constexpr (RAD == 4) {
+    const cpx<R> v0 = v[0], v1 = v[S], v2 = v[2 * S], v3 = v[3 * S];
     const cpx<R> s02 = {v0.x + v2.x, v0.y + v2.y}, d02 = {v0.x - v2.x, v0.y - v2.y};
     const cpx<R> s13 = {v1.x + v3.x, v1.y + v3.y}, d13 = {v1.x - v3.x, v1.y - v3.y};
     const cpx<R> jd = {-(R)DIR * d13.y, (R)DIR * d13.x};   // DIR * i * d13
-    const int o = (b / Ns) * Ns * 4 + k;
-    dst[o] = {s02.x + s13.x, s02.y + s13.y};
-    dst[o + Ns] = {d02.x + jd.x, d02.y + jd.y};
-    dst[o + 2 * Ns] = {s02.x - s13.x, s02.y - s13.y};
-    dst[o + 3 * Ns] = {d02.x - jd.x, d02.y - jd.y};
-  }
-}
-
-template <typename R, int DIR>
-__device__ inline void stage3(const cpx<R>* src, cpx<R>* dst, int N, int Ns, const R* tw, int lane, int team) {
-  const int nb = N / 3, ts = N / (Ns * 3);
-  const R h3 = (R)0.86602540378443864676;
-  for (int b = lane; b < nb; b += team) {
-    const int k = b % Ns;
-    const cpx<R> v0 = src[b];
-    const cpx<R> v1 = twiddle<R, DIR>(src[b + nb], tw, k * ts);
-    const cpx<R> v2 = twiddle<R, DIR>(src[b + 2 * nb], tw, 2 * k * ts);
+    v[0] = {s02.x + s13.x, s02.y + s13.y};
+    v[S] = {d02.x + jd.x, d02.y + jd.y};
+    v[2 * S] = {s02.x - s13.x, s02.y - s13.y};
+    v[3 * S] = {d02.x - jd.x, d02.y - jd.y};
+  } else if constexpr (RAD == 3) {
+    const R h3 = (R)0.86602540378443864676;
+    const cpx<R> v0 = v[0], v1 = v[S], v2 = v[2 * S];
     const cpx<R> s12 = {v1.x + v2.x, v1.y + v2.y}, d12 = {v1.x - v2.x, v1.y - v2.y};
     const cpx<R> m = {v0.x - (R)0.5 * s12.x, v0.y - (R)0.5 * s12.y};
-    const cpx<R> jd = {-(R)DIR * h3 * d12.y, (R)DIR * h3 * d12.x};
-    const int o = (b / Ns) * Ns * 3 + k;
-    dst[o] = {v0.x + s12.x, v0.y + s12.y};
-    dst[o + Ns] = {m.x + jd.x, m.y + jd.y};
-    dst[o + 2 * Ns] = {m.x - jd.x, m.y - jd.y};
+    const R h = (R)DIR * h3;   // m + DIR i h3 d12, m - DIR i h3 d12
+    v[0] = {v0.x + s12.x, v0.y + s12.y};
+    v[S] = {fmadd(-h, d12.y, m.x), fmadd(h, d12.x, m.y)};
+    v[2 * S] = {fmadd(h, d12.y, m.x), fmadd(-h, d12.x, m.y)};
+  } else if constexpr (RAD == 5) {
+    // with t1 = v1 + v4, t2 = v2 + v3, t3 = v1 - v4, t4 = v2 - v3 (c_q, s_q the cosine and
+    // sine of 2 pi q / 5): X1,4 = v0 + c1 t1 + c2 t2 +- DIR i (s1 t3 + s2 t4),
+    // X2,3 = v0 + c2 t1 + c1 t2 +- DIR i (s2 t3 - s1 t4), X0 = v0 + t1 + t2
+    const R c1 = (R)0.30901699437494742410, c2 = (R)-0.80901699437494742410;
+    const R s1 = (R)0.95105651629515357212, s2 = (R)0.58778525229247312917;
+    const cpx<R> v0 = v[0], v1 = v[S], v2 = v[2 * S], v3 = v[3 * S], v4 = v[4 * S];
+    const cpx<R> t1 = {v1.x + v4.x, v1.y + v4.y}, t2 = {v2.x + v3.x, v2.y + v3.y};
+    const cpx<R> t3 = {v1.x - v4.x, v1.y - v4.y}, t4 = {v2.x - v3.x, v2.y - v3.y};
+    const cpx<R> a1 = {fmadd(c2, t2.x, fmadd(c1, t1.x, v0.x)), fmadd(c2, t2.y, fmadd(c1, t1.y, v0.y))};
+    const cpx<R> a2 = {fmadd(c1, t2.x, fmadd(c2, t1.x, v0.x)), fmadd(c1, t2.y, fmadd(c2, t1.y, v0.y))};
+    const cpx<R> b1 = {fmadd(s2, t4.x, s1 * t3.x), fmadd(s2, t4.y, s1 * t3.y)};
+    const cpx<R> b2 = {fmadd(s2, t3.x, -(s1 * t4.x)), fmadd(s2, t3.y, -(s1 * t4.y))};
+    const cpx<R> j1 = {-(R)DIR * b1.y, (R)DIR * b1.x}, j2 = {-(R)DIR * b2.y, (R)DIR * b2.x};   // DIR i b
+    v[0] = {v0.x + t1.x + t2.x, v0.y + t1.y + t2.y};
+    v[S] = {a1.x + j1.x, a1.y + j1.y};
+    v[4 * S] = {a1.x - j1.x, a1.y - j1.y};
+    v[2 * S] = {a2.x + j2.x, a2.y + j2.y};
+    v[3 * S] = {a2.x - j2.x, a2.y - j2.y};
   }
 }
 
-// radix 5: with t1 = v1 + v4, t2 = v2 + v3, t3 = v1 - v4, t4 = v2 - v3 (c_q, s_q the cosine
-// and sine of 2 pi q / 5): X1,4 = v0 + c1 t1 + c2 t2 +- DIR i (s1 t3 + s2 t4),
-// X2,3 = v0 + c2 t1 + c1 t2 +- DIR i (s2 t3 - s1 t4), X0 = v0 + t1 + t2
-template <typename R, int DIR>
-__device__ inline void bfly5(const cpx<R> v[5], cpx<R> out[5]) {
-  const R c1 = (R)0.30901699437494742410, c2 = (R)-0.80901699437494742410;
-  const R s1 = (R)0.95105651629515357212, s2 = (R)0.58778525229247312917;
-  const cpx<R> t1 = {v[1].x + v[4].x, v[1].y + v[4].y}, t2 = {v[2].x + v[3].x, v[2].y + v[3].y};
-  const cpx<R> t3 = {v[1].x - v[4].x, v[1].y - v[4].y}, t4 = {v[2].x - v[3].x, v[2].y - v[3].y};
-  const cpx<R> a1 = {v[0].x + c1 * t1.x + c2 * t2.x, v[0].y + c1 * t1.y + c2 * t2.y};
-  const cpx<R> a2 = {v[0].x + c2 * t1.x + c1 * t2.x, v[0].y + c2 * t1.y + c1 * t2.y};
-  const cpx<R> b1 = {s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y};
-  const cpx<R> b2 = {s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y};
-  const cpx<R> j1 = {-(R)DIR * b1.y, (R)DIR * b1.x}, j2 = {-(R)DIR * b2.y, (R)DIR * b2.x};   // DIR i b
-  out[0] = {v[0].x + t1.x + t2.x, v[0].y + t1.y + t2.y};
-  out[1] = {a1.x + j1.x, a1.y + j1.y};
-  out[4] = {a1.x - j1.x, a1.y - j1.y};
-  out[2] = {a2.x + j2.x, a2.y + j2.y};
-  out[3] = {a2.x - j2.x, a2.y - j2.y};
-}
-
-template <typename R, int DIR>
-__device__ inline void stage5(const cpx<R>* src, cpx<R>* dst, int N, int Ns, const R* tw, int lane, int team) {
-  const int nb = N / 5, ts = N / (Ns * 5);
-  for (int b = lane; b < nb; b += team) {
-    const int k = b % Ns;
-    cpx<R> v[5], o5[5];
-    v[0] = src[b];
+// Both stages of a pair on the points v[e] = x[b + e N / (R1 R2)] of group b = j Ns + k, k < Ns:
+// the stage of radix R1 (sub-transforms of Ns points) joins v[q2], v[q2 + R2], .., the stage of
+// radix R2 (of Ns R1) joins v[q R2], v[q R2 + 1], ..  Output q + p R1 of the pair, at v[p + q R2],
+// belongs at j Ns R1 R2 + k + (q + p R1) Ns.  ts = N / (Ns R1 R2).  FIRST: Ns = 1, k = 0, where the
+// first stage's twiddle factors are 1.
+template <typename R, int DIR, int R1, int R2, bool FIRST>
+__device__ __forceinline__ void stage_pair(cpx<R>* v, int k, int Ns, int ts, const R* __restrict__ tw) {
+  if constexpr (!FIRST) {
+    const int i1 = k * ts * R2;
 #pragma unroll
-    for (int q = 1; q < 5; ++q) v[q] = twiddle<R, DIR>(src[b + q * nb], tw, q * k * ts);
-    bfly5<R, DIR>(v, o5);
-    const int o = (b / Ns) * Ns * 5 + k;
+    for (int q = 1; q < R1; ++q)
 #pragma unroll
-    for (int q = 0; q < 5; ++q) dst[o + q * Ns] = o5[q];
+      for (int q2 = 0; q2 < R2; ++q2) v[q2 + q * R2] = twiddle<R, DIR>(v[q2 + q * R2], tw, q * i1);
   }
-}
-
-template <typename R, int DIR>
-__device__ cpx<R>* stockham(cpx<R>* src, cpx<R>* dst, const FftPlan& P, const R* __restrict__ tw, int lane, int team) {
-  const int N = P.n;
-  int Ns = 1;
-  for (int s = 0; s < P.nst; ++s) {
-    const int r = P.rad[s];
-    if (r == 4) stage4<R, DIR>(src, dst, N, Ns, tw, lane, team);
-    else if (r == 2) stage2<R, DIR>(src, dst, N, Ns, tw, lane, team);
-    else if (r == 3) stage3<R, DIR>(src, dst, N, Ns, tw, lane, team);
-    else stage5<R, DIR>(src, dst, N, Ns, tw, lane, team);
-    __syncthreads();
-    cpx<R>* t = src;
-    src = dst;
-    dst = t;
-    Ns *= r;
-  }
-  return src;
-}
-
-// In-place Stockham for long strided lines, where the line groups of the ping-pong form are
-// too narrow to fill a cache line: one LDS buffer holds twice the lines.  Each stage first
-// reads every butterfly of the thread into registers (at most PPT / RAD of them, PPT = the
-// points per thread that the launch guarantees), then, after a barrier, writes the outputs
-// over the same buffer.
-template <typename R, int DIR, int RAD, int BPT>
-__device__ inline void stage_ip(cpx<R>* buf, int N, int Ns, const R* tw, int lane, int team) {
-  const int nb = N / RAD, ts = N / (Ns * RAD);
-  cpx<R> v[BPT][RAD];
 #pragma unroll
-  for (int t = 0; t < BPT; ++t) {
-    const int b = lane + t * team;
-    if (b < nb) {
-      const int k = b % Ns;
-      v[t][0] = buf[b];
+  for (int q2 = 0; q2 < R2; ++q2) butterfly<R, DIR, R1, R2>(v + q2);
+  if constexpr (R2 > 1) {
 #pragma unroll
-      for (int q = 1; q < RAD; ++q) v[t][q] = twiddle<R, DIR>(buf[b + q * nb], tw, q * k * ts);
-    }
-  }
-  __syncthreads();
+    for (int q = 0; q < R1; ++q) {
+      const int i2 = FIRST ? q * ts : k * ts + q * (Ns * ts);
+      if (!FIRST || q > 0) {
 #pragma unroll
-  for (int t = 0; t < BPT; ++t) {
-    const int b = lane + t * team;
-    if (b < nb) {
-      const int k = b % Ns;
-      const int o = (b / Ns) * Ns * RAD + k;
-      if (RAD == 2) {
-        const cpx<R> v0 = v[t][0], v1 = v[t][1];
-        buf[o] = {v0.x + v1.x, v0.y + v1.y};
-        buf[o + Ns] = {v0.x - v1.x, v0.y - v1.y};
-      } else if (RAD == 4) {
-        const cpx<R> v0 = v[t][0], v1 = v[t][1], v2 = v[t][2], v3 = v[t][3];
-        const cpx<R> s02 = {v0.x + v2.x, v0.y + v2.y}, d02 = {v0.x - v2.x, v0.y - v2.y};
-        const cpx<R> s13 = {v1.x + v3.x, v1.y + v3.y}, d13 = {v1.x - v3.x, v1.y - v3.y};
-        const cpx<R> jd = {-(R)DIR * d13.y, (R)DIR * d13.x};   // DIR * i * d13
-        buf[o] = {s02.x + s13.x, s02.y + s13.y};
-        buf[o + Ns] = {d02.x + jd.x, d02.y + jd.y};
-        buf[o + 2 * Ns] = {s02.x - s13.x, s02.y - s13.y};
-        buf[o + 3 * Ns] = {d02.x - jd.x, d02.y - jd.y};
-      } else if (RAD == 5) {
-        cpx<R> o5[5];
-        bfly5<R, DIR>(v[t], o5);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) buf[o + q * Ns] = o5[q];
-      } else {
-        const R h3 = (R)0.86602540378443864676;
-        const cpx<R> v0 = v[t][0], v1 = v[t][1], v2 = v[t][RAD - 1];
-        const cpx<R> s12 = {v1.x + v2.x, v1.y + v2.y}, d12 = {v1.x - v2.x, v1.y - v2.y};
-        const cpx<R> m = {v0.x - (R)0.5 * s12.x, v0.y - (R)0.5 * s12.y};
-        const cpx<R> jd = {-(R)DIR * h3 * d12.y, (R)DIR * h3 * d12.x};
-        buf[o] = {v0.x + s12.x, v0.y + s12.y};
-        buf[o + Ns] = {m.x + jd.x, m.y + jd.y};
-        buf[o + 2 * Ns] = {m.x - jd.x, m.y - jd.y};
+        for (int q2 = 1; q2 < R2; ++q2) v[q2 + q * R2] = twiddle<R, DIR>(v[q2 + q * R2], tw, q2 * i2);
       }
+      butterfly<R, DIR, R2, 1>(v + q * R2);
     }
   }
-  __syncthreads();
 }
 
-template <typename R, int DIR, int PPT>
-__device__ cpx<R>* stockham_ip(cpx<R>* buf, const FftPlan& P, const R* __restrict__ tw, int lane, int team) {
-  const int N = P.n;
-  int Ns = 1;
-  for (int s = 0; s < P.nst; ++s) {
-    const int r = P.rad[s];
-    if (r == 4) stage_ip<R, DIR, 4, (PPT + 3) / 4>(buf, N, Ns, tw, lane, team);
-    else if (r == 2) stage_ip<R, DIR, 2, (PPT + 1) / 2>(buf, N, Ns, tw, lane, team);
-    else if (r == 3) stage_ip<R, DIR, 3, (PPT + 2) / 3>(buf, N, Ns, tw, lane, team);
-    else stage_ip<R, DIR, 5, (PPT + 4) / 5>(buf, N, Ns, tw, lane, team);
-    Ns *= r;
-  }
-  return buf;
+// First pass: in(i) is input point i, out(o, z) takes point o of the pass's result.  SYNC: the
+// input lies where the output goes; at most one group per thread then (fft_team), read before
+// the barrier and written after it.
+template <typename R, int DIR, int R1, int R2, bool SYNC, typename In, typename Out>
+__device__ __forceinline__ void pass_first(int N, const R* __restrict__ tw, int lane, int team, In in, Out out) {
+  constexpr int RR = R1 * R2;
+  const int M = N / RR;
+  auto group = [&](int b) {
+    cpx<R> v[RR];
+    if (b < M) {
+#pragma unroll
+      for (int e = 0; e < RR; ++e) v[e] = in(b + e * M);
+    }
+    if (SYNC) __syncthreads();
+    if (b < M) {
+      stage_pair<R, DIR, R1, R2, true>(v, 0, 1, M, tw);
+#pragma unroll
+      for (int q = 0; q < R1; ++q)
+#pragma unroll
+        for (int p = 0; p < R2; ++p) out(b * RR + q + p * R1, v[p + q * R2]);
+    }
+  };
+  if constexpr (SYNC) group(lane);
+  else
+    for (int b = lane; b < M; b += team) group(b);
 }
+
+// Later pass (MID: of radix 4 x 4, before the last), its input in LDS; SYNC as above, with
+// all groups of a thread held in registers over the barrier.
+template <typename R, int DIR, int R1, int R2, bool MID, bool SYNC, typename In, typename Out>
+__device__ __forceinline__ void pass_next(int N, int Ns, const R* __restrict__ tw, int lane, int team, In in, Out out) {
+  constexpr int RR = R1 * R2, BPT = SYNC ? (15 + RR) / RR : 1;
+  const int M = N / RR;
+  cpx<R> v[BPT][RR];
+  auto read = [&](cpx<R>* x, int b) {
+#pragma unroll
+    for (int e = 0; e < RR; ++e) x[e] = in(b + e * M);
+  };
+  auto finish = [&](cpx<R>* x, int b) {
+    const int j = MID ? b / Ns : 0, k = MID ? b - j * Ns : b, o = MID ? j * Ns * RR + k : b;
+    const int st = MID ? Ns : M;
+    stage_pair<R, DIR, R1, R2, false>(x, k, st, MID ? M / Ns : 1, tw);
+#pragma unroll
+    for (int q = 0; q < R1; ++q)
+#pragma unroll
+      for (int p = 0; p < R2; ++p) out(o + (q + p * R1) * st, x[p + q * R2]);
+  };
+  if constexpr (SYNC) {
+#pragma unroll
+    for (int t = 0; t < BPT; ++t)
+      if (lane + t * team < M) read(v[t], lane + t * team);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < BPT; ++t)
+      if (lane + t * team < M) finish(v[t], lane + t * team);
+  } else {
+    for (int b = lane; b < M; b += team) {
+      read(v[0], b);
+      finish(v[0], b);
+    }
+  }
+}
+
+// A whole transform of the team's N points: in(i) and out(o, z) as above, ld(i) and st(i, z) its
+// N points of LDS.  SYNC_IN: `in` reads those points themselves; SYNC_OUT: `out` writes them.
+// Every thread of the block comes through here (barriers); no barrier follows the last write.
+template <typename R, int DIR, bool SYNC_IN, bool SYNC_OUT, typename In, typename Out, typename Ld, typename St>
+__device__ __forceinline__ void transform(const FftPlan& P, const R* __restrict__ tw, int lane, int team, In in,
+                                          Out out, Ld ld, St st) {
+  const int N = P.n;
+  int Ns = P.pass[0] / 10 * (P.pass[0] % 10);
+  switch (P.pass[0]) {
+    case 44: pass_first<R, DIR, 4, 4, SYNC_IN>(N, tw, lane, team, in, st); break;
+    case 53: pass_first<R, DIR, 5, 3, SYNC_IN>(N, tw, lane, team, in, st); break;
+    case 54: pass_first<R, DIR, 5, 4, SYNC_IN>(N, tw, lane, team, in, st); break;
+    case 34: pass_first<R, DIR, 3, 4, SYNC_IN>(N, tw, lane, team, in, st); break;
+    case 51: pass_first<R, DIR, 5, 1, SYNC_IN>(N, tw, lane, team, in, st); break;
+    case 31: pass_first<R, DIR, 3, 1, SYNC_IN>(N, tw, lane, team, in, st); break;
+    default: pass_first<R, DIR, 4, 1, SYNC_IN>(N, tw, lane, team, in, st); break;   // 41
+  }
+  __syncthreads();
+  for (int s = 1; s + 1 < P.np; ++s) {
+    pass_next<R, DIR, 4, 4, true, true>(N, Ns, tw, lane, team, ld, st);
+    __syncthreads();
+    Ns *= 16;
+  }
+  switch (P.pass[P.np - 1]) {
+    case 44: pass_next<R, DIR, 4, 4, false, SYNC_OUT>(N, Ns, tw, lane, team, ld, out); break;
+    case 42: pass_next<R, DIR, 4, 2, false, SYNC_OUT>(N, Ns, tw, lane, team, ld, out); break;
+    case 34: pass_next<R, DIR, 3, 4, false, SYNC_OUT>(N, Ns, tw, lane, team, ld, out); break;
+    case 41: pass_next<R, DIR, 4, 1, false, SYNC_OUT>(N, Ns, tw, lane, team, ld, out); break;
+    case 32: pass_next<R, DIR, 3, 2, false, SYNC_OUT>(N, Ns, tw, lane, team, ld, out); break;
+    case 31: pass_next<R, DIR, 3, 1, false, SYNC_OUT>(N, Ns, tw, lane, team, ld, out); break;
+    case 21: pass_next<R, DIR, 2, 1, false, SYNC_OUT>(N, Ns, tw, lane, team, ld, out); break;
+    default:   // 11: the points as they are
+      for (int i = lane; i < N; i += team) out(i, ld(i));
+  }
+}
+
+// two neighbouring values, the first of any alignment
+template <typename T>
+struct pair2 {
+  T x, y;
+};
+template <typename T>
+__device__ inline pair2<T> load2(const T* p) {
+  typedef T vec __attribute__((ext_vector_type(2), aligned(alignof(T))));
+  const vec v = *reinterpret_cast<const vec*>(p);
+  return {v.x, v.y};
+}
+
+// LDS position of point i of a transform: one point of padding after every 16, so that the
+// strided writes of the first pass spread over the banks
+__host__ __device__ inline int fft_pos(int i) { return i + (i >> 4); }
 
 template <typename T>
 __device__ inline const T* twsel(const double* d, const float* f);
@@ -251,75 +293,84 @@ template <>
 __device__ inline const float* twsel<float>(const double*, const float* f) { return f; }
 
 // ============================================================================ forward x
-// MODE 0: f = D u* scaled; MODE 1: f given (les_poisson).
+// MODE 0: f = D u* scaled; MODE 1: f given (les_poisson).  The rows go through LDS before the
+// first pass: the divergence reads eleven values a point, too many to hold for the 16 or 20
+// points of a group (that spilled).  Bound by those loads: the divergence of 1024 x 512 x 256 in
+// FP32 641 us with a load an instruction, 476 with two points a load (2.1 GB, 4.5 TB/s); 512 x
+// 256 x 128 in FP64 144 -> 141.  npair_blk teams of blockDim /
+// npair_blk threads (a power of two), one row pair each.
 template <typename T, int MODE>
 __device__ __forceinline__ void rfftx_body(dim3 bid, GridP g, const FftPlan& P, const T* __restrict__ us, const T* __restrict__ vs,
                                                const T* __restrict__ ws, const T* __restrict__ fin,
                                                cpx<T>* __restrict__ spec, const double* __restrict__ twd,
                                                const float* __restrict__ twf, const double* __restrict__ dtp,
                                                double gamma, int npair_blk, double* __restrict__ bulk_part) {
-  extern __shared__ unsigned char smem_raw[];
-  cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
   const int nx = g.nx, nxh = nx / 2 + 1, nyh = g.ny / 2;
-  cpx<T>* B = A + npair_blk * nx;
-  const int64_t npairs = (int64_t)g.nz * nyh;
+  const int npairs = g.nz * nyh;   // pair indices fit 32 bits
   // gamma = 0: the plain divergence (initial projection), no time factor
   const T scale = (MODE == 0 && gamma > 0.0) ? (T)(1.0 / (gamma * dtp[0])) : (T)1;
+  const int team = blockDim.x / npair_blk, tsh = __builtin_ctz(team);
+  const int p = threadIdx.x >> tsh, lane = threadIdx.x & (team - 1);
+  cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw) + p * fft_pos(nx);
+  const int gp = (int)bid.x * npair_blk + p;
+  const bool ok = gp < npairs;
+  // teams past the last pair repeat pair 0 and store nothing
+  const int kk = ok ? gp / nyh : 0, j0 = ok ? 2 * (gp - kk * nyh) : 0, k = kk + 1;
+  const int64_t c0 = idx3(g, k, j0, 0);
   double bsum = 0.0;
-  for (int e = threadIdx.x; e < npair_blk * nx; e += blockDim.x) {
-    const int p = e / nx, i = e % nx;
-    const int64_t gp = (int64_t)bid.x * npair_blk + p;
-    cpx<T> z = {(T)0, (T)0};
-    if (gp < npairs) {
-      const int k = (int)gp / nyh + 1;
-      const int j0 = 2 * ((int)gp % nyh);
-      T fv[2];
-      for (int r = 0; r < 2; ++r) {
-        const int j = j0 + r;
-        const int64_t c = idx3(g, k, j, i);
-        if (MODE == 0) {
-          const T d = (us[c] - us[idx3(g, k, j, wrap_m(i, nx))]) * (T)g.rdx +
-                      (vs[c] - ((g.ywall && j == 0) ? (T)0 : vs[idx3(g, k, wrap_m(j, g.ny), i)])) * (T)g.rdy +
-                      (ws[c] - ((k == 1 && g.zbc == LES_ZBC_PERIODIC) ? ws[idx3(g, g.nz, j, i)] : ws[c - g.sxy])) *
-                          (T)g.rdzf[k];
-          fv[r] = d * scale;
-          if (bulk_part) bsum += (double)us[c] * g.dzf[k];
-        } else {
-          fv[r] = fin[c];
-        }
+  auto ld = [&](int i) { return A[fft_pos(i)]; };
+  auto st = [&](int i, cpx<T> z) { A[fft_pos(i)] = z; };
+  if (MODE == 0) {
+    const T *u0 = us + c0, *v0 = vs + c0, *w0 = ws + c0;
+    const bool ylow = g.ywall && j0 == 0;   // no face below the first row of a duct
+    const T* vm = ylow ? v0 : vs + idx3(g, k, wrap_m(j0, g.ny), 0);
+    const T* wm = (k == 1 && g.zbc == LES_ZBC_PERIODIC) ? ws + idx3(g, g.nz, j0, 0) : w0 - g.sxy;
+    const T rdx = (T)g.rdx, rdy = (T)g.rdy, rdz = (T)g.rdzf[k];
+    const double dz = g.dzf[k];
+    // two points at a time (nx is even): nine 2-wide loads and two single ones
+#pragma unroll 2
+    for (int i = 2 * lane; i < nx; i += 2 * team) {
+      const int im = wrap_m(i, nx);
+      const pair2<T> ua = load2(u0 + i), ub = load2(u0 + nx + i), va = load2(v0 + i), vb = load2(v0 + nx + i);
+      const pair2<T> wa = load2(w0 + i), wb = load2(w0 + nx + i), wc = load2(wm + i), wd = load2(wm + nx + i);
+      const T uc = u0[im], ud = u0[nx + im];
+      pair2<T> vc = load2(vm + i);
+      if (ylow) vc = {(T)0, (T)0};
+      auto div = [&](T du, T dv, T dw) { return fmadd(dw, rdz, fmadd(du, rdx, dv * rdy)) * scale; };
+      A[fft_pos(i)] = {div(ua.x - uc, va.x - vc.x, wa.x - wc.x), div(ub.x - ud, vb.x - va.x, wb.x - wd.x)};
+      A[fft_pos(i + 1)] = {div(ua.y - ua.x, va.y - vc.y, wa.y - wc.y), div(ub.y - ub.x, vb.y - va.y, wb.y - wd.y)};
+      if (bulk_part) {
+        bsum += (double)ua.x * dz;
+        bsum += (double)ub.x * dz;
+        bsum += (double)ua.y * dz;
+        bsum += (double)ub.y * dz;
       }
-      z = {fv[0], fv[1]};
     }
-    A[e] = z;
+  } else {
+    const T* f0 = fin + c0;
+#pragma unroll 4
+    for (int i = lane; i < nx; i += team) A[fft_pos(i)] = {f0[i], f0[nx + i]};
   }
-  if (bulk_part) {
+  __syncthreads();
+  transform<T, -1, true, true>(P, twsel<T>(twd, twf), lane, team, ld, st, ld, st);
+  if (MODE == 0 && bulk_part) {
     __shared__ double red[256];
-    red[threadIdx.x] = bsum;
+    red[threadIdx.x] = ok ? bsum : 0.0;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
+    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
       if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
       __syncthreads();
     }
     if (threadIdx.x == 0) bulk_part[bid.x] = red[0];
   }
   __syncthreads();
-  const int team = blockDim.x / npair_blk;
-  const int p = threadIdx.x / team, lane = threadIdx.x % team;
-  cpx<T>* res = nullptr;
-  {
-    const T* tw = twsel<T>(twd, twf);
-    res = stockham<T, -1>(A + p * nx, B + p * nx, P, tw, lane, team);
-  }
-  // res points into A or B for team p (same parity for all teams)
-  const int64_t gp = (int64_t)bid.x * npair_blk + p;
-  if (gp >= npairs) return;
-  const int k = (int)gp / nyh;
-  const int j0 = 2 * ((int)gp % nyh);
-  cpx<T>* s0 = spec + ((int64_t)k * g.ny + j0) * g.nxp;
+  if (!ok) return;
+  cpx<T>* s0 = spec + ((int64_t)kk * g.ny + j0) * g.nxp;
   cpx<T>* s1 = s0 + g.nxp;
   for (int l = lane; l < nxh; l += team) {
-    const cpx<T> a = res[l];
-    const cpx<T> b = res[(nx - l) % nx];
+    const cpx<T> a = A[fft_pos(l)];
+    const cpx<T> b = A[fft_pos(l == 0 ? 0 : nx - l)];
     // A_l = (Z_l + conj Z_{N-l})/2, B_l = (Z_l - conj Z_{N-l})/(2i)
     s0[l] = {(T)0.5 * (a.x + b.x), (T)0.5 * (a.y - b.y)};
     s1[l] = {(T)0.5 * (a.y + b.y), (T)0.5 * (b.x - a.x)};
@@ -347,56 +398,35 @@ template <typename T>
 __device__ __forceinline__ void irfftx_body(dim3 bid, GridP g, const FftPlan& P, const cpx<T>* __restrict__ spec,
                                                 T* __restrict__ out, const double* __restrict__ twd,
                                                 const float* __restrict__ twf, int npair_blk) {
-  extern __shared__ unsigned char smem_raw[];
-  cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
   const int nx = g.nx, nxh = nx / 2 + 1, nyh = g.ny / 2;
-  cpx<T>* B = A + npair_blk * nx;
-  const int64_t npairs = (int64_t)g.nz * nyh;
-  // Hermitian reconstruction of two rows' spectra; loads in batches of four per thread,
-  // all issued before their LDS stores
-  const int total = npair_blk * nx;
-  for (int e0 = 0; e0 < total; e0 += 4 * (int)blockDim.x) {
-    cpx<T> va[4], vb[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int e = e0 + b * (int)blockDim.x + (int)threadIdx.x;
-      const int p = e / nx, l = e % nx;
-      const int64_t gp = (int64_t)bid.x * npair_blk + p;
-      const bool ok = e < total && gp < npairs;
-      const int64_t k = ok ? (int)gp / nyh : 0;   // pair indices fit 32 bits
-      const int j0 = ok ? 2 * ((int)gp % nyh) : 0;
-      const int ls = l < nxh ? l : nx - l;
-      const cpx<T>* s0 = spec + (k * g.ny + j0) * g.nxp;
-      va[b] = s0[ls];
-      vb[b] = s0[g.nxp + ls];
+  const int npairs = g.nz * nyh;   // pair indices fit 32 bits
+  const int team = blockDim.x / npair_blk, tsh = __builtin_ctz(team);
+  const int p = threadIdx.x >> tsh, lane = threadIdx.x & (team - 1);
+  cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw) + p * fft_pos(nx);
+  const int gp = (int)bid.x * npair_blk + p;
+  const bool ok = gp < npairs;
+  // teams past the last pair repeat pair 0 and store nothing
+  const int kk = ok ? gp / nyh : 0, j0 = ok ? 2 * (gp - kk * nyh) : 0;
+  const cpx<T>* s0 = spec + ((int64_t)kk * g.ny + j0) * g.nxp;
+  const cpx<T>* s1 = s0 + g.nxp;
+  T* o0 = out + idx3(g, kk + 1, j0, 0);
+  T* o1 = o0 + nx;
+  // Hermitian reconstruction of two rows' spectra
+  auto in = [&](int l) -> cpx<T> {
+    const int ls = l < nxh ? l : nx - l;
+    const cpx<T> a = s0[ls], b = s1[ls];
+    return l < nxh ? cpx<T>{a.x - b.y, a.y + b.x} : cpx<T>{a.x + b.y, -a.y + b.x};
+  };
+  auto put = [&](int i, cpx<T> z) {
+    if (ok) {
+      o0[i] = z.x;
+      o1[i] = z.y;
     }
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int e = e0 + b * (int)blockDim.x + (int)threadIdx.x;
-      if (e >= total) continue;
-      const int p = e / nx, l = e % nx;
-      const int64_t gp = (int64_t)bid.x * npair_blk + p;
-      cpx<T> z = {(T)0, (T)0};
-      if (gp < npairs) {
-        const cpx<T> a = va[b], bb = vb[b];
-        z = l < nxh ? cpx<T>{a.x - bb.y, a.y + bb.x} : cpx<T>{a.x + bb.y, -a.y + bb.x};
-      }
-      A[e] = z;
-    }
-  }
-  __syncthreads();
-  const int team = blockDim.x / npair_blk;
-  const int p = threadIdx.x / team, lane = threadIdx.x % team;
-  const T* tw = twsel<T>(twd, twf);
-  cpx<T>* res = stockham<T, 1>(A + p * nx, B + p * nx, P, tw, lane, team);
-  const int64_t gp = (int64_t)bid.x * npair_blk + p;
-  if (gp >= npairs) return;
-  const int k = (int)gp / nyh + 1;
-  const int j0 = 2 * ((int)gp % nyh);
-  for (int i = lane; i < nx; i += team) {
-    out[idx3(g, k, j0, i)] = res[i].x;
-    out[idx3(g, k, j0 + 1, i)] = res[i].y;
-  }
+  };
+  auto ld = [&](int i) { return A[fft_pos(i)]; };
+  auto st = [&](int i, cpx<T> z) { A[fft_pos(i)] = z; };
+  transform<T, 1, false, false>(P, twsel<T>(twd, twf), lane, team, in, put, ld, st);
 }
 
 template <typename T>
@@ -432,7 +462,7 @@ __global__ void __launch_bounds__(256) kb_irfftx(BatchMap m) {
 // V_{N-m}) / 2 with W_m = exp(-i pi m / (2N)) and V its FFT; inverse, V_m = conj(W_m) (X_m -
 // i X_{N-m}) (X_N = 0) before the inverse FFT, whose output is stored back in the permuted
 // order.  twc holds (cos, sin)(pi m / (2N)).
-template <typename T, int DIR, bool SOLVE, int PPT = 0, int DCT = 0>
+template <typename T, int DIR, bool SOLVE, int DCT = 0>
 __device__ __forceinline__ void fft_lines_body(dim3 bid, const FftPlan& P, cpx<T>* __restrict__ data, int nl, int64_t lstride,
                                                    int64_t ostride, int L, const double* __restrict__ twd,
                                                    const float* __restrict__ twf, const double* __restrict__ lamx,
@@ -440,115 +470,72 @@ __device__ __forceinline__ void fft_lines_body(dim3 bid, const FftPlan& P, cpx<T
                                                    double norm, const double* __restrict__ dtp = nullptr,
                                                    double hg = 0.0, const double* __restrict__ twcd = nullptr,
                                                    const float* __restrict__ twcf = nullptr) {
-  extern __shared__ unsigned char smem_raw[];
-  cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
-  const int N = P.n;
-  const int NP = N + 1;   // padded line stride in LDS (spreads the l-interleaved stores over banks)
-  cpx<T>* B = A + L * NP;
-  const int l0 = bid.x * L;
-  const int o = bid.y;
-  cpx<T>* base = data + (int64_t)o * ostride;
-  // loads in batches of LB per thread, all issued before their LDS stores (out-of-range lanes
-  // read element 0 and store zero): four, or in FP32 with the in-place form all PPT points of
-  // the thread at once (measured faster there; slower in FP64)
-  constexpr int LB = (sizeof(T) == 4 && PPT > 0) ? PPT : 4;
-  const int total = L * N;
-  for (int e0 = 0; e0 < total; e0 += LB * (int)blockDim.x) {
-    cpx<T> v[LB];
-#pragma unroll
-    for (int b = 0; b < LB; ++b) {
-      const int e = e0 + b * (int)blockDim.x + (int)threadIdx.x;
-      const int t = e / L, l = l0 + e % L;
-      const bool ok = e < total && l < nl;
-      v[b] = base[ok ? (int64_t)t * lstride + l : 0];
-      if (!ok) v[b] = cpx<T>{(T)0, (T)0};
-    }
-#pragma unroll
-    for (int b = 0; b < LB; ++b) {
-      const int e = e0 + b * (int)blockDim.x + (int)threadIdx.x;
-      if (e < total) {
-        const int t = e / L;
-        // forward cosine transform: even points first, then odd points in reverse
-        const int pos = (DCT && DIR < 0) ? ((t & 1) ? N - 1 - (t >> 1) : (t >> 1)) : t;
-        A[(e % L) * NP + pos] = v[b];
-      }
-    }
-  }
-  __syncthreads();
-  const int team = blockDim.x / L;
-  const int ll = threadIdx.x / team, lane = threadIdx.x % team;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  // neighbouring threads take neighbouring lines, in global memory and in LDS
+  const int N = P.n, lsh = __builtin_ctz(L), team = blockDim.x >> lsh;
+  const int ll = threadIdx.x & (L - 1), lane = threadIdx.x >> lsh;
+  cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw) + ll;
+  const int l = (int)bid.x * L + ll;
+  const bool ok = l < nl;
+  // lines past the last repeat line 0 and store nothing
+  cpx<T>* base = data + (int64_t)bid.y * ostride + (ok ? l : 0);
   const T* tw = twsel<T>(twd, twf);
   const T* twc = DCT ? twsel<T>(twcd, twcf) : nullptr;
-  if (DCT && DIR > 0) {
-    // inverse cosine transform: V_m = conj(W_m) (X_m - i X_{N-m}), pairs (m, N - m) in place
-    cpx<T>* X = A + ll * NP;
-    for (int m = lane; m <= N / 2; m += team) {
-      const cpx<T> a = X[m];
-      const cpx<T> b = m == 0 ? cpx<T>{(T)0, (T)0} : X[N - m];
-      {
-        const T c = twc[2 * m], sn = twc[2 * m + 1];
-        const T zx = a.x + b.y, zy = a.y - b.x;
-        X[m] = {c * zx - sn * zy, sn * zx + c * zy};
-      }
-      if (m > 0 && 2 * m != N) {
-        const T c = twc[2 * (N - m)], sn = twc[2 * (N - m) + 1];
-        const T zx = b.x + a.y, zy = b.y - a.x;
-        X[N - m] = {c * zx - sn * zy, sn * zx + c * zy};
-      }
-    }
-    __syncthreads();
-  }
-  cpx<T>* res;
-  if constexpr (PPT > 0) res = stockham_ip<T, DIR, PPT>(A + ll * NP, P, tw, lane, team);
-  else res = stockham<T, DIR>(A + ll * NP, B + ll * NP, P, tw, lane, team);
-  if (SOLVE) {
-    // res holds the z spectrum of column (l, m = o); o indexes y modes here
-    const int l = l0 + ll;
+  auto ld = [&](int i) { return A[fft_pos(i) << lsh]; };
+  auto st = [&](int i, cpx<T> z) { A[fft_pos(i) << lsh] = z; };
+  auto get = [&](int t) { return base[(int64_t)t * lstride]; };
+  auto put = [&](int t, cpx<T> z) {
+    if (ok) base[(int64_t)t * lstride] = z;
+  };
+  if constexpr (SOLVE) {
+    // the transforms are along z here, bid.y indexes the y modes
     const double hc = hg != 0.0 ? hg * dtp[0] : 0.0;
-    for (int t = lane; t < N; t += team) {
-      double lam = (l < nl ? lamx[l] : 0.0) + lamy[o] + lamz[t];
-      double f = hg != 0.0 ? norm / (1.0 - hc * lam) : ((lam != 0.0) ? norm / lam : 0.0);
-      res[t].x = (T)((double)res[t].x * f);
-      res[t].y = (T)((double)res[t].y * f);
-    }
+    const double lxy = (ok ? lamx[l] : 0.0) + lamy[bid.y];
+    auto scaled = [&](int t, cpx<T> z) {
+      const double lam = lxy + lamz[t];
+      const double f = hg != 0.0 ? norm / (1.0 - hc * lam) : ((lam != 0.0) ? norm / lam : 0.0);
+      st(t, cpx<T>{(T)((double)z.x * f), (T)((double)z.y * f)});
+    };
+    transform<T, DIR, false, true>(P, tw, lane, team, get, scaled, ld, st);
     __syncthreads();
-    if constexpr (PPT > 0) {
-      res = stockham_ip<T, 1, PPT>(res, P, tw, lane, team);
-    } else {
-      cpx<T>* other = (res == A + ll * NP) ? B + ll * NP : A + ll * NP;
-      res = stockham<T, 1>(res, other, P, tw, lane, team);
-    }
-  }
-  // every team's result lies in the same buffer (A or B)
-  cpx<T>* R = (res == A + ll * NP) ? A : B;
-  __syncthreads();
-  for (int e = threadIdx.x; e < L * N; e += blockDim.x) {
-    const int t = e / L, l2 = e % L;
-    const int l = l0 + l2;
-    if (l >= nl) continue;
-    if (DCT && DIR < 0) {
+    transform<T, 1, true, false>(P, tw, lane, team, ld, put, ld, st);
+  } else if constexpr (DCT && DIR < 0) {
+    // forward cosine transform: even points first, then odd points in reverse
+    auto perm = [&](int i) { return get(2 * i < N ? 2 * i : 2 * (N - 1 - i) + 1); };
+    transform<T, DIR, false, true>(P, tw, lane, team, perm, st, ld, st);
+    __syncthreads();
+    for (int t = lane; t < N; t += team) {
       // X_t = (W_t V_t + conj(W_t) V_{N-t}) / 2
-      const cpx<T> a = R[l2 * NP + t], b = R[l2 * NP + (t == 0 ? 0 : N - t)];
+      const cpx<T> a = ld(t), b = ld(t == 0 ? 0 : N - t);
       const T c = twc[2 * t], sn = twc[2 * t + 1];
-      const T xr = (c * a.x + sn * a.y) + (c * b.x - sn * b.y);
-      const T xi = (c * a.y - sn * a.x) + (c * b.y + sn * b.x);
-      base[(int64_t)t * lstride + l] = {(T)0.5 * xr, (T)0.5 * xi};
-    } else if (DCT) {
-      base[(int64_t)t * lstride + l] = R[l2 * NP + ((t & 1) ? N - 1 - (t >> 1) : (t >> 1))];
-    } else {
-      base[(int64_t)t * lstride + l] = R[l2 * NP + t];
+      const cpx<T> wa = turn(a, c, -sn), wb = turn(b, c, sn);
+      put(t, cpx<T>{(T)0.5 * (wa.x + wb.x), (T)0.5 * (wa.y + wb.y)});
     }
+  } else if constexpr (DCT) {
+    // inverse cosine transform: V_m = conj(W_m) (X_m - i X_{N-m})
+#pragma unroll 8
+    for (int t = lane; t < N; t += team) st(t, get(t));
+    __syncthreads();
+    auto pre = [&](int m) -> cpx<T> {
+      const cpx<T> a = ld(m);
+      const cpx<T> b = m == 0 ? cpx<T>{(T)0, (T)0} : ld(N - m);
+      return turn(cpx<T>{a.x + b.y, a.y - b.x}, twc[2 * m], twc[2 * m + 1]);
+    };
+    auto perm = [&](int i, cpx<T> z) { put(2 * i < N ? 2 * i : 2 * (N - 1 - i) + 1, z); };
+    transform<T, DIR, true, false>(P, tw, lane, team, pre, perm, ld, st);
+  } else {
+    transform<T, DIR, false, false>(P, tw, lane, team, get, put, ld, st);
   }
 }
 
-template <typename T, int DIR, bool SOLVE, int PPT = 0, int DCT = 0>
+template <typename T, int DIR, bool SOLVE, int DCT = 0>
 __global__ void __launch_bounds__(256) k_fft_lines(FftPlan P, cpx<T>* data, int nl, int64_t lstride, int64_t ostride,
                                                    int L, const double* twd, const float* twf, const double* lamx,
                                                    const double* lamy, const double* lamz, double norm,
                                                    const double* dtp, double hg, const double* twcd,
                                                    const float* twcf) {
-  fft_lines_body<T, DIR, SOLVE, PPT, DCT>(blockIdx, P, data, nl, lstride, ostride, L, twd, twf, lamx, lamy, lamz, norm,
-                                          dtp, hg, twcd, twcf);
+  fft_lines_body<T, DIR, SOLVE, DCT>(blockIdx, P, data, nl, lstride, ostride, L, twd, twf, lamx, lamy, lamz, norm,
+                                     dtp, hg, twcd, twcf);
 }
 
 // Batched y transforms (SOLVE = false) or periodic-z spectral solve (SOLVE = true).
@@ -732,12 +719,12 @@ __global__ void __launch_bounds__(256) k_irfftx3(GridP g, FftPlan P, const cpx<T
   irfftx_body<T>(dim3(blockIdx.x), g, P, spec + comp * cstride, f, twd, twf, npair_blk);
 }
 
-template <typename T, int DIR, bool SOLVE, int PPT = 0>
+template <typename T, int DIR, bool SOLVE>
 __global__ void __launch_bounds__(256) k_fft_lines3(FftPlan P, cpx<T>* data, int64_t cstride, int nl, int64_t lstride,
                                                     int64_t ostride, int L, const double* twd, const float* twf,
                                                     const double* lamx, const double* lamy, const double* lamz,
                                                     double norm, const double* dtp, double hg) {
-  fft_lines_body<T, DIR, SOLVE, PPT>(dim3(blockIdx.x, blockIdx.y), P, data + blockIdx.z * cstride, nl, lstride, ostride,
+  fft_lines_body<T, DIR, SOLVE>(dim3(blockIdx.x, blockIdx.y), P, data + blockIdx.z * cstride, nl, lstride, ostride,
                                      L, twd, twf, lamx, lamy, lamz, norm, dtp, hg);
 }
 
@@ -788,7 +775,7 @@ __global__ void __launch_bounds__(256) k_helm3d_factor(GridP g, const double* __
 
 // ============================================================================ bulk
 // s = (U_b - <u*>) / <q>, <.> the dzf-weighted volume mean; stored in dt[1].  One block:
-// strided partial sums per thread, then a fixed-order tree (deterministic).
+// 256 strided partial sums, then a fixed-order tree (deterministic).
 struct BulkArgs {
   const double* part;
   int nblk;
@@ -805,19 +792,21 @@ __device__ __forceinline__ void bulk_final_body(const BulkArgs& a_, double (*sm)
   const int nblk = a_.nblk, nz = a_.nz;
   const double* q = a_.q;
   const double* dzf = a_.dzf;
-  double a = 0.0, b = 0.0, d = 0.0;
-  for (int i = threadIdx.x; i < nblk; i += 256) a += part[i];
-  for (int k = threadIdx.x; k < nz; k += 256) {
-    b += q[k] * dzf[k + 1];
-    d += dzf[k + 1];
+  for (int t = threadIdx.x; t < 256; t += blockDim.x) {
+    double a = 0.0, b = 0.0, d = 0.0;
+    for (int i = t; i < nblk; i += 256) a += part[i];
+    for (int k = t; k < nz; k += 256) {
+      b += q[k] * dzf[k + 1];
+      d += dzf[k + 1];
+    }
+    sm[0][t] = a;
+    sm[1][t] = b;
+    sm[2][t] = d;
   }
-  sm[0][threadIdx.x] = a;
-  sm[1][threadIdx.x] = b;
-  sm[2][threadIdx.x] = d;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st)
-      for (int r = 0; r < 3; ++r) sm[r][threadIdx.x] += sm[r][threadIdx.x + st];
+    for (int t = threadIdx.x; t < st; t += blockDim.x)
+      for (int r = 0; r < 3; ++r) sm[r][t] += sm[r][t + st];
     __syncthreads();
   }
   if (threadIdx.x == 0) {
@@ -828,7 +817,7 @@ __device__ __forceinline__ void bulk_final_body(const BulkArgs& a_, double (*sm)
 
 // Forward y transform with the flow-rate shift folded in: block (0, 0), dispatched first,
 // forms s from the forward-x partials while the others transform (plane = blockIdx.y - 1).
-template <typename T, int PPT = 0, int DCT = 0>
+template <typename T, int DCT = 0>
 __global__ void __launch_bounds__(256) k_ffty_bulk(FftPlan P, cpx<T>* data, int nl, int64_t lstride, int64_t ostride,
                                                    int L, const double* twd, const float* twf, const double* lamx,
                                                    const double* lamy, const double* lamz, BulkArgs ba,
@@ -838,7 +827,7 @@ __global__ void __launch_bounds__(256) k_ffty_bulk(FftPlan P, cpx<T>* data, int 
     if (blockIdx.x == 0) bulk_final_body(ba, reinterpret_cast<double(*)[256]>(smem_raw));
     return;
   }
-  fft_lines_body<T, -1, false, PPT, DCT>(dim3(blockIdx.x, blockIdx.y - 1), P, data, nl, lstride, ostride, L, twd, twf,
+  fft_lines_body<T, -1, false, DCT>(dim3(blockIdx.x, blockIdx.y - 1), P, data, nl, lstride, ostride, L, twd, twf,
                                          lamx, lamy, lamz, 1.0, nullptr, 0.0, twcd, twcf);
 }
 
@@ -858,74 +847,53 @@ __global__ void k_scalar_ghosts(GridP g, T* f) {
 }
 
 // ============================================================================ launchers
-// Transforms per 256-thread block: a power of two (so the block splits into equal teams)
-// with at most 1024 complex points per buffer (two buffers: <= 32 KiB in double; larger
-// tiles measured slower on the channel workload).
-static int pow2_floor(int v) {
-  int p = 1;
-  while (p * 2 <= v) p *= 2;
-  return p;
-}
-static int pairs_per_block(int nx) {
-  // rows of 256 points and more: two row pairs per block (measured faster than four on the
-  // 256 x 128 x 96 channel; shorter rows keep up to eight)
-  int p = pow2_floor(std::max(1, (nx >= 256 ? 512 : 1024) / nx));
-  return std::min(p, 8);
-}
-static int lines_per_block(int n) {
-  int L = pow2_floor(std::max(1, 1024 / n));
-  return std::min(L, 32);
-}
-
-// Line groups of the single-field strided transforms: the ping-pong form (two buffers of
-// L <= 1024 / n lines), unless its row segments of L consecutive l stay under 128 bytes (one
-// cache line; long lines); then the in-place form with up to four times the lines (L n <=
-// 4096, one buffer within 64 KB), ppt = L n / 256 points per thread rounded up to 8 or 16.
-struct LineShape {
-  int L, ppt;      // ppt 0: ping-pong
+// Row pairs per block of the x transforms: blocks of 128 threads (eight pairs of 256 points).
+// 64 and 256 threads, or 256 of which half only load, took 525-750 us where 128 take 475 (forward
+// x of 1024 x 512 x 256 in FP32) and within 2 us of it on 25 MB of 256 x 128 x 96.
+struct RowShape {
+  int pairs, nt;
   size_t sh;       // dynamic LDS bytes
 };
-static LineShape line_shape(int n, size_t esz) {
-  const int Lpp = lines_per_block(n);
-  if ((size_t)Lpp * esz >= 128 || n > 4096) return {Lpp, 0, 2 * (size_t)Lpp * (n + 1) * esz};
-  int L = Lpp;
-  while (L < 32 && (size_t)(2 * L) * n <= 4096 && (size_t)(2 * L) * (n + 1) * esz <= 65536) L *= 2;
-  const int ppt = L * n / 256 <= 8 ? 8 : 16;
-  return {L, ppt, (size_t)L * (n + 1) * esz};
+static RowShape row_shape(int n, size_t esz) {
+  const int team = fft_team(n), pairs = std::max(1, 128 / team);
+  return {pairs, pairs * team, (size_t)pairs * fft_pos(n) * esz};
+}
+
+// Lines per block of the strided transforms: neighbouring values of 128 bytes, one cache line
+// (256 bytes were no faster), more while a block has fewer than 64 threads, fewer where it would
+// have more than 256 (`want`: at most that many, whatever the cache line).
+struct LineShape {
+  int L, nt;
+  size_t sh;
+};
+static LineShape line_shape(int n, size_t esz, int want = 0) {
+  const int team = fft_team(n);
+  int L = want ? want : (int)(128 / esz);
+  while (!want && L * team < 64) L *= 2;
+  while (L * team > 256) L /= 2;
+  return {L, std::max(64, L * team), (size_t)L * fft_pos(n) * esz};
 }
 
 template <typename T>
 static void fwd_x(Ctx& c, int mode, const T* us, const T* vs, const T* ws, const T* fin, double gamma, bool bulk) {
   const FftPlan P = make_plan(c.g.nx);
-  const int pb = pairs_per_block(c.g.nx);
+  const RowShape rs = row_shape(c.g.nx, sizeof(cpx<T>));
   const int64_t npairs = (int64_t)c.g.nz * (c.g.ny / 2);
-  const unsigned nblk = (unsigned)((npairs + pb - 1) / pb);
-  const size_t sh = 2 * (size_t)pb * c.g.nx * sizeof(cpx<T>);
+  const unsigned nblk = (unsigned)((npairs + rs.pairs - 1) / rs.pairs);
   double* bp = bulk ? c.t.bulk : nullptr;
   const double spec_bytes = (double)(c.g.nx / 2 + 1) * c.g.ny * c.g.nz * 2 * sizeof(T);
   const double in_bytes = (mode == 0 ? 3.0 : 1.0) * c.g.sxy * c.g.nz * sizeof(T);
   if (mode == 0)
-    LES_LAUNCH(c, "rfftx_div", in_bytes + spec_bytes, (k_rfftx<T, 0>), dim3(nblk), dim3(256), sh, c.g, P, us, vs, ws, fin,
-                       (cpx<T>*)c.spec, c.t.twx, c.t.twx_f, c.t.dt, gamma, pb, bp);
+    LES_LAUNCH(c, "rfftx_div", in_bytes + spec_bytes, (k_rfftx<T, 0>), dim3(nblk), dim3(rs.nt), rs.sh, c.g, P, us, vs, ws, fin,
+                       (cpx<T>*)c.spec, c.t.twx, c.t.twx_f, c.t.dt, gamma, rs.pairs, bp);
   else
-    LES_LAUNCH(c, "rfftx", in_bytes + spec_bytes, (k_rfftx<T, 1>), dim3(nblk), dim3(256), sh, c.g, P, us, vs, ws, fin,
-                       (cpx<T>*)c.spec, c.t.twx, c.t.twx_f, c.t.dt, gamma, pb, bp);
+    LES_LAUNCH(c, "rfftx", in_bytes + spec_bytes, (k_rfftx<T, 1>), dim3(nblk), dim3(rs.nt), rs.sh, c.g, P, us, vs, ws, fin,
+                       (cpx<T>*)c.spec, c.t.twx, c.t.twx_f, c.t.dt, gamma, rs.pairs, bp);
   // the flow-rate shift is formed by an extra block of the forward y transform that follows
   c.bulk_nblk = bulk ? (int)nblk : 0;
 }
 
 // y transforms of the spectrum buffer (DIR -1 forward, +1 inverse)
-template <typename T, int DIR, bool SOLVE, int DCT = 0>
-static decltype(&k_fft_lines<T, DIR, SOLVE, 0, DCT>) lines_kernel(int ppt) {
-  return ppt == 0 ? k_fft_lines<T, DIR, SOLVE, 0, DCT>
-                  : (ppt == 8 ? k_fft_lines<T, DIR, SOLVE, 8, DCT> : k_fft_lines<T, DIR, SOLVE, 16, DCT>);
-}
-template <typename T, int DIR, bool SOLVE>
-static decltype(&k_fft_lines3<T, DIR, SOLVE, 0>) lines3_kernel(int ppt) {
-  return ppt == 0 ? k_fft_lines3<T, DIR, SOLVE, 0>
-                  : (ppt == 8 ? k_fft_lines3<T, DIR, SOLVE, 8> : k_fft_lines3<T, DIR, SOLVE, 16>);
-}
-
 template <typename T, int DIR>
 static void ffty(Ctx& c, const char* name) {
   const int nxh = c.g.nx / 2 + 1;
@@ -936,8 +904,8 @@ static void ffty(Ctx& c, const char* name) {
   const int L = ls.L;
   dim3 grid((nxh + L - 1) / L, nz);
   // ducts: the cosine transform of the wall-bounded y direction
-  auto kern = c.g.ywall ? lines_kernel<T, DIR, false, 1>(ls.ppt) : lines_kernel<T, DIR, false, 0>(ls.ppt);
-  LES_LAUNCH(c, name, 2 * spec_bytes, kern, grid, dim3(256), ls.sh, P, (cpx<T>*)c.spec, nxh, (int64_t)c.g.nxp,
+  auto kern = c.g.ywall ? k_fft_lines<T, DIR, false, 1> : k_fft_lines<T, DIR, false, 0>;
+  LES_LAUNCH(c, name, 2 * spec_bytes, kern, grid, dim3(ls.nt), ls.sh, P, (cpx<T>*)c.spec, nxh, (int64_t)c.g.nxp,
              (int64_t)c.g.nxp * ny, L, c.t.twy, c.t.twy_f, c.t.lamx, c.t.lamy, c.t.lamz, 1.0, nullptr, 0.0, c.t.twc,
              c.t.twc_f);
 }
@@ -953,7 +921,7 @@ static void fftz_solve(Ctx& c, const char* name, double hg) {
   const int L = ls.L;
   dim3 grid((nxh + L - 1) / L, ny);
   const double norm = 1.0 / ((double)c.g.nx * ny * nz);
-  LES_LAUNCH(c, name, 2 * spec_bytes, (lines_kernel<T, -1, true>(ls.ppt)), grid, dim3(256), ls.sh, P,
+  LES_LAUNCH(c, name, 2 * spec_bytes, (k_fft_lines<T, -1, true>), grid, dim3(ls.nt), ls.sh, P,
              (cpx<T>*)c.spec, nxh, (int64_t)c.g.nxp * ny, (int64_t)c.g.nxp, L, c.t.twz, c.t.twz_f, c.t.lamx, c.t.lamy,
              c.t.lamz, norm, c.t.dt, hg, (const double*)nullptr, (const float*)nullptr);
 }
@@ -972,9 +940,8 @@ static void spectral_solve(Ctx& c) {
     const size_t sh = std::max(ls.sh, 3 * 256 * sizeof(double));
     const BulkArgs ba{c.t.bulk, c.bulk_nblk, c.t.dt, c.t.hfac + 4 * nz, c.t.dzf, nz, c.cfg.ubulk,
                       (double)c.g.nx * c.g.ny, c.cfg.lz};
-    auto kern = c.g.ywall ? (ls.ppt == 0 ? k_ffty_bulk<T, 0, 1> : (ls.ppt == 8 ? k_ffty_bulk<T, 8, 1> : k_ffty_bulk<T, 16, 1>))
-                          : (ls.ppt == 0 ? k_ffty_bulk<T, 0, 0> : (ls.ppt == 8 ? k_ffty_bulk<T, 8, 0> : k_ffty_bulk<T, 16, 0>));
-    LES_LAUNCH(c, "ffty_fwd", 2 * spec_bytes, kern, grid, dim3(256), sh, P, sp, nxh, (int64_t)c.g.nxp,
+    auto kern = c.g.ywall ? k_ffty_bulk<T, 1> : k_ffty_bulk<T, 0>;
+    LES_LAUNCH(c, "ffty_fwd", 2 * spec_bytes, kern, grid, dim3(ls.nt), sh, P, sp, nxh, (int64_t)c.g.nxp,
                (int64_t)c.g.nxp * ny, L, c.t.twy, c.t.twy_f, c.t.lamx, c.t.lamy, c.t.lamz, ba, c.t.twc, c.t.twc_f);
     c.bulk_nblk = 0;
   } else {
@@ -1005,14 +972,12 @@ static void spectral_solve(Ctx& c) {
 template <typename T>
 static void inv_x(Ctx& c, T* out) {
   const FftPlan P = make_plan(c.g.nx);
-  const int pb = pairs_per_block(c.g.nx);
+  const RowShape rs = row_shape(c.g.nx, sizeof(cpx<T>));
   const int64_t npairs = (int64_t)c.g.nz * (c.g.ny / 2);
-  const unsigned nblk = (unsigned)((npairs + pb - 1) / pb);
-  const size_t sh = 2 * (size_t)pb * c.g.nx * sizeof(cpx<T>);
+  const unsigned nblk = (unsigned)((npairs + rs.pairs - 1) / rs.pairs);
   const double spec_bytes = (double)(c.g.nx / 2 + 1) * c.g.ny * c.g.nz * 2 * sizeof(T);
-  LES_LAUNCH(c, "irfftx", spec_bytes + (double)c.g.sxy * c.g.nz * sizeof(T), (k_irfftx<T>), dim3(nblk), dim3(256), sh,
-             c.g, P, (const cpx<T>*)c.spec, out,
-                     c.t.twx, c.t.twx_f, pb);
+  LES_LAUNCH(c, "irfftx", spec_bytes + (double)c.g.sxy * c.g.nz * sizeof(T), (k_irfftx<T>), dim3(nblk),
+             dim3(rs.nt), rs.sh, c.g, P, (const cpx<T>*)c.spec, out, c.t.twx, c.t.twx_f, rs.pairs);
 }
 
 // Crank-Nicolson in all directions (Eq. onestar_imp3d): the predicted components u*, v*, w*
@@ -1035,26 +1000,25 @@ void launch_helmholtz_3d(Ctx& c, int stage) {
   // forward x of the three components
   {
     const FftPlan P = make_plan(nx);
-    const int pb = pairs_per_block(nx);
+    const RowShape rs = row_shape(nx, sizeof(cpx<T>));
     const int64_t npairs = (int64_t)n * (ny / 2);
-    const size_t sh = 2 * (size_t)pb * nx * sizeof(cpx<T>);
     LES_LAUNCH(c, "h3d_rfftx", 3 * (spec_bytes + (double)c.g.sxy * n * sizeof(T)), (k_rfftx3<T>),
-               dim3((unsigned)((npairs + pb - 1) / pb), 3), dim3(256), sh, c.g, P, (const T*)c.us, (const T*)c.vs,
-               (const T*)c.wsf, sp, cstride, c.t.twx, c.t.twx_f, pb);
+               dim3((unsigned)((npairs + rs.pairs - 1) / rs.pairs), 3), dim3(rs.nt), rs.sh, c.g, P, (const T*)c.us, (const T*)c.vs,
+               (const T*)c.wsf, sp, cstride, c.t.twx, c.t.twx_f, rs.pairs);
   }
   const FftPlan Py = make_plan(ny);
   const LineShape lsy = line_shape(ny, sizeof(cpx<T>));
   const int Ly = lsy.L;
   const dim3 gy((nxh + Ly - 1) / Ly, n, 3);
-  LES_LAUNCH(c, "h3d_ffty_fwd", 6 * spec_bytes, (lines3_kernel<T, -1, false>(lsy.ppt)), gy, dim3(256), lsy.sh, Py, sp,
+  LES_LAUNCH(c, "h3d_ffty_fwd", 6 * spec_bytes, (k_fft_lines3<T, -1, false>), gy, dim3(lsy.nt), lsy.sh, Py, sp,
              cstride, nxh, (int64_t)c.g.nxp, (int64_t)c.g.nxp * ny, Ly, c.t.twy, c.t.twy_f, c.t.lamx, c.t.lamy,
              c.t.lamz, 1.0, nullptr, 0.0);
   if (c.cfg.zbc == LES_ZBC_PERIODIC) {
     const FftPlan Pz = make_plan(n);
     const LineShape lsz = line_shape(n, sizeof(cpx<T>));
     const int Lz = lsz.L;
-    LES_LAUNCH(c, "h3d_fftz_solve", 6 * spec_bytes, (lines3_kernel<T, -1, true>(lsz.ppt)),
-               dim3((nxh + Lz - 1) / Lz, ny, 3), dim3(256), lsz.sh, Pz, sp, cstride, nxh, (int64_t)c.g.nxp * ny,
+    LES_LAUNCH(c, "h3d_fftz_solve", 6 * spec_bytes, (k_fft_lines3<T, -1, true>),
+               dim3((nxh + Lz - 1) / Lz, ny, 3), dim3(lsz.nt), lsz.sh, Pz, sp, cstride, nxh, (int64_t)c.g.nxp * ny,
                (int64_t)c.g.nxp, Lz, c.t.twz, c.t.twz_f, c.t.lamx, c.t.lamy, c.t.lamz, 1.0 / ((double)nx * ny * n),
                c.t.dt, hg);
   } else {
@@ -1077,17 +1041,16 @@ void launch_helmholtz_3d(Ctx& c, int stage) {
       sh.S == 8 ? go(k_thomas_scan3<T, 8, 32>, (nchain + 32 - 1) / 32)
                 : go(k_thomas_scan3<T, 16, 32>, (nchain + 32 - 1) / 32);
   }
-  LES_LAUNCH(c, "h3d_ffty_inv", 6 * spec_bytes, (lines3_kernel<T, 1, false>(lsy.ppt)), gy, dim3(256), lsy.sh, Py, sp,
+  LES_LAUNCH(c, "h3d_ffty_inv", 6 * spec_bytes, (k_fft_lines3<T, 1, false>), gy, dim3(lsy.nt), lsy.sh, Py, sp,
              cstride, nxh, (int64_t)c.g.nxp, (int64_t)c.g.nxp * ny, Ly, c.t.twy, c.t.twy_f, c.t.lamx, c.t.lamy,
              c.t.lamz, 1.0, nullptr, 0.0);
   {
     const FftPlan P = make_plan(nx);
-    const int pb = pairs_per_block(nx);
+    const RowShape rs = row_shape(nx, sizeof(cpx<T>));
     const int64_t npairs = (int64_t)n * (ny / 2);
-    const size_t sh = 2 * (size_t)pb * nx * sizeof(cpx<T>);
     LES_LAUNCH(c, "h3d_irfftx", 3 * (spec_bytes + (double)c.g.sxy * n * sizeof(T)), (k_irfftx3<T>),
-               dim3((unsigned)((npairs + pb - 1) / pb), 3), dim3(256), sh, c.g, P, (const cpx<T>*)sp, cstride,
-               (T*)c.us, (T*)c.vs, (T*)c.wsf, c.t.twx, c.t.twx_f, pb);
+               dim3((unsigned)((npairs + rs.pairs - 1) / rs.pairs), 3), dim3(rs.nt), rs.sh, c.g, P, (const cpx<T>*)sp, cstride,
+               (T*)c.us, (T*)c.vs, (T*)c.wsf, c.t.twx, c.t.twx_f, rs.pairs);
   }
 }
 
@@ -1205,20 +1168,26 @@ void launch_project(Ctx& c) {
 
 // ============================================================================ batch launchers
 template <typename T>
-void batch_poisson(hipStream_t st, const BatchMap& m, const int* totals, size_t sh_x, size_t sh_y, size_t sh_z,
-                   int stage) {
+void batch_poisson(hipStream_t st, const BatchMap& m, const int* totals, const FftLaunch* f, int stage) {
   static const double G[3] = {8.0 / 15.0, 2.0 / 15.0, 1.0 / 3.0};
-  hipLaunchKernelGGL(kb_rfftx<T>, dim3(totals[BK_RFFTX]), dim3(256), sh_x, st, m, G[stage]);
-  hipLaunchKernelGGL((kb_fft_lines<T, -1, false>), dim3(totals[BK_FFTY]), dim3(256), sh_y, st, m);
-  hipLaunchKernelGGL((kb_fft_lines<T, -1, true>), dim3(totals[BK_FFTZ]), dim3(256), sh_z, st, m);
-  hipLaunchKernelGGL((kb_fft_lines<T, 1, false>), dim3(totals[BK_FFTY]), dim3(256), sh_y, st, m);
-  hipLaunchKernelGGL(kb_irfftx<T>, dim3(totals[BK_RFFTX]), dim3(256), sh_x, st, m);
+  hipLaunchKernelGGL(kb_rfftx<T>, dim3(totals[BK_RFFTX]), dim3(f[0].nt), f[0].sh, st, m, G[stage]);
+  hipLaunchKernelGGL((kb_fft_lines<T, -1, false>), dim3(totals[BK_FFTY]), dim3(f[1].nt), f[1].sh, st, m);
+  hipLaunchKernelGGL((kb_fft_lines<T, -1, true>), dim3(totals[BK_FFTZ]), dim3(f[2].nt), f[2].sh, st, m);
+  hipLaunchKernelGGL((kb_fft_lines<T, 1, false>), dim3(totals[BK_FFTY]), dim3(f[1].nt), f[1].sh, st, m);
+  hipLaunchKernelGGL(kb_irfftx<T>, dim3(totals[BK_RFFTX]), dim3(f[0].nt), f[0].sh, st, m);
 }
-template void batch_poisson<float>(hipStream_t, const BatchMap&, const int*, size_t, size_t, size_t, int);
-template void batch_poisson<double>(hipStream_t, const BatchMap&, const int*, size_t, size_t, size_t, int);
+template void batch_poisson<float>(hipStream_t, const BatchMap&, const int*, const FftLaunch*, int);
+template void batch_poisson<double>(hipStream_t, const BatchMap&, const int*, const FftLaunch*, int);
 
-int fft_pairs_per_block(int nx) { return pairs_per_block(nx); }
-int fft_lines_per_block(int n) { return lines_per_block(n); }
+// shapes of a box in a batch, whose launches take the largest block and LDS of their boxes
+FftLaunch fft_rows(int n, size_t esz) {
+  const RowShape r = row_shape(n, esz);
+  return {r.pairs, r.nt, r.sh};
+}
+FftLaunch fft_lines(int n, size_t esz, int want) {
+  const LineShape l = line_shape(n, esz, want);
+  return {l.L, l.nt, l.sh};
+}
 
 #define INST(T)                                                                              \
   template void launch_poisson_rhs_fwd<T>(Ctx&, const T*, const T*, const T*, double, int); \
