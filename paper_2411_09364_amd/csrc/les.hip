@@ -286,14 +286,14 @@ size_t carve(Ctx& c, char* base) {
   const size_t nxp = ((size_t)(f.nx / 2 + 1) + rq - 1) / rq * rq;
   // one spectrum buffer; three with CN in all directions (the components are solved together)
   c.spec = take(nxp * f.ny * n * 2 * E * (f.implicit_z == LES_VISC_CN_3D ? 3 : 1));
-  // factor pairs of the z systems of every (l, m) column with its own factors (walls only)
-  t.pfac = (double*)take(f.zbc == LES_ZBC_PERIODIC ? 0 : nxp * factor_modes(c.g) * n * 2 * 8);
+  // factors of the z systems of every (l, m) column with its own (walls only)
+  t.pfac = (double*)take(f.zbc == LES_ZBC_PERIODIC ? 0 : nxp * factor_modes(c.g) * n * 8);
   // long-run statistics: running sums and series, per-sample partials
   t.stats = (double*)take(8 * stats_words(c.g));
   t.stats_part = (double*)take(8 * stats_part_words(n, (int64_t)f.nx * f.ny));
-  // per-substep factor pairs of the Helmholtz z systems (CN in all directions, walls)
-  t.hfac3 = (double2*)take(f.zbc != LES_ZBC_PERIODIC && f.implicit_z == LES_VISC_CN_3D
-                               ? 2 * nxp * (f.ny / 2 + 1) * n * 16 : 0);
+  // per-substep factors of the Helmholtz z systems (CN in all directions, walls)
+  t.hfac3 = (double*)take(f.zbc != LES_ZBC_PERIODIC && f.implicit_z == LES_VISC_CN_3D
+                              ? 2 * nxp * (f.ny / 2 + 1) * n * 8 : 0);
   return off;
 }
 

@@ -133,24 +133,27 @@ __device__ inline dim3 xcd_tile(dim3 bid, dim3 grid) {
   return dim3(tt % grid.x, tt / grid.x, bid.z);
 }
 
-// Segmented-scan solve of tridiagonal chains with known factors (Thomas sweeps written as
-// first-order linear recurrences: forward d_k = r_k f_k + alpha_k d_{k-1}, alpha_k = -a_k r_k,
-// r_k = 1/pivot; back x_k = d_k - c'_k x_{k+1}).  The CG chains of a block are cut into
-// segments of S rows, thread (cl, p) holding rows k0 = p S .. k0 + S - 1 (< n) of chain cl in
-// v.  Each sweep runs over the segment from a zero start while carrying the product of its
-// coefficients; the segment end values are folded in order through E, G ([segments][CG] in
-// LDS) and every row is corrected by product x start value.  R(j), A(j), C(j) give r, a and
-// c' of row k0 + j.  Contains barriers: every thread of the block calls it.
+// Segmented-scan solve of tridiagonal systems with known factors and two right-hand sides, the
+// real and imaginary parts (Thomas sweeps written as first-order linear recurrences: forward
+// d_k = r_k f_k + alpha_k d_{k-1}, alpha_k = -a_k r_k, r_k = 1/pivot; back x_k = d_k - c'_k
+// x_{k+1}).  The CG systems of a block are cut into segments of S rows, thread (cl, p) holding
+// rows k0 = p S .. k0 + S - 1 (< n) of system cl in v.  Each sweep runs over the segment from a
+// zero start while carrying the product of its coefficients; the segment end values are folded
+// in order through E, G ([segments][CG] in LDS) and every row is corrected by product x start
+// value.  R(j), A(j), C(j) give r, a and c' of row k0 + j.  Contains barriers: every thread of
+// the block calls it.
 template <int S, int CG, class RF, class AF, class CF>
-__device__ __forceinline__ void seg_scan_solve(double (&v)[S], int k0, int n, int p, int P, int cl,
-                                               double (*E)[CG], double (*G)[CG], const RF& R, const AF& A,
+__device__ __forceinline__ void seg_scan_solve(double2 (&v)[S], int k0, int n, int p, int P, int cl,
+                                               double2 (*E)[CG], double (*G)[CG], const RF& R, const AF& A,
                                                const CF& C) {
-  double dl = 0.0, pr = 1.0;
+  double2 dl = make_double2(0.0, 0.0);
+  double pr = 1.0;
 #pragma unroll
   for (int j = 0; j < S; ++j) {
     if (k0 + j < n) {
       const double al = -A(j) * R(j);
-      dl = R(j) * v[j] + al * dl;
+      dl.x = __builtin_fma(R(j), v[j].x, al * dl.x);
+      dl.y = __builtin_fma(R(j), v[j].y, al * dl.y);
       pr = al * pr;
       v[j] = dl;
     }
@@ -158,21 +161,27 @@ __device__ __forceinline__ void seg_scan_solve(double (&v)[S], int k0, int n, in
   E[p][cl] = dl;
   G[p][cl] = pr;
   __syncthreads();
-  double D = 0.0;
-  for (int q = 0; q < p; ++q) D = E[q][cl] + G[q][cl] * D;
+  double2 D = make_double2(0.0, 0.0);
+  for (int q = 0; q < p; ++q) {
+    D.x = E[q][cl].x + G[q][cl] * D.x;
+    D.y = E[q][cl].y + G[q][cl] * D.y;
+  }
   pr = 1.0;
 #pragma unroll
   for (int j = 0; j < S; ++j) {
     if (k0 + j < n) {
       pr *= -A(j) * R(j);
-      v[j] += pr * D;
+      v[j].x += pr * D.x;
+      v[j].y += pr * D.y;
     }
   }
-  double xl = 0.0, ps = 1.0;
+  double2 xl = make_double2(0.0, 0.0);
+  double ps = 1.0;
 #pragma unroll
   for (int j = S - 1; j >= 0; --j) {
     if (k0 + j < n) {
-      xl = v[j] - C(j) * xl;
+      xl.x = v[j].x - C(j) * xl.x;
+      xl.y = v[j].y - C(j) * xl.y;
       ps = -C(j) * ps;
       v[j] = xl;
     }
@@ -181,14 +190,18 @@ __device__ __forceinline__ void seg_scan_solve(double (&v)[S], int k0, int n, in
   E[p][cl] = xl;
   G[p][cl] = ps;
   __syncthreads();
-  double X = 0.0;
-  for (int q = P - 1; q > p; --q) X = E[q][cl] + G[q][cl] * X;
+  double2 X = make_double2(0.0, 0.0);
+  for (int q = P - 1; q > p; --q) {
+    X.x = E[q][cl].x + G[q][cl] * X.x;
+    X.y = E[q][cl].y + G[q][cl] * X.y;
+  }
   ps = 1.0;
 #pragma unroll
   for (int j = S - 1; j >= 0; --j) {
     if (k0 + j < n) {
       ps *= -C(j);
-      v[j] += ps * X;
+      v[j].x += ps * X.x;
+      v[j].y += ps * X.y;
     }
   }
 }
@@ -228,7 +241,7 @@ struct Tables {
   float* twx_f;     // float copies
   float* twy_f;
   float* twz_f;
-  double2* hfac3;   // CN in all directions, walls: per-substep z factor pairs, u/v rows then w rows,
+  double* hfac3;    // CN in all directions, walls: per-substep 1/pivot of the z systems, u/v rows then w rows,
                     //   each [nz][ny/2+1][nxp]
   double* hfac;     // 12*nz: CN factorisation: c', 1/pivot for u/v rows and for w rows, the
                     //   flow-rate profile q, unused, sub-diagonals (u/v, w), diagonals and
@@ -245,7 +258,7 @@ struct Tables {
   float* twc_f;
   double* dsm_part; // plane partial sums (LM, MM) per tile and wave of the fused dynamic model
   double* cflc;     // 4 per block of the last correction: max |u|/dx + |v|/dy + |w|/dzf per wave
-  double* pfac;     // walls: (c', 1/pivot) of the (l, m) z systems, [nz][nm][nxp] pairs with
+  double* pfac;     // walls: 1/pivot of the (l, m) z systems, [nz][nm][nxp] with
                     //   nm = ny/2+1 (periodic y: m and ny - m share them) or ny (ducts)
   double* stats;    // statistics: header[8], sums [11][nz], wall-stress series [cap][2]
   double* stats_part; // per-block plane partials of one sample [nz+1][nblk][11]

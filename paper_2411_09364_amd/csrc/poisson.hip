@@ -555,13 +555,14 @@ __global__ void __launch_bounds__(256) kb_fft_lines(BatchMap m) {
 
 // Factorisation of the z systems of every (l, m) column (Sec. 2.2: one tridiagonal system
 // per wavenumber pair), once per grid: the Poisson matrix depends on the geometry only, so
-// c'_k = c_k / p_k and 1/p_k, p_k = b_k + lambda_x(l) + lambda_y(m) - a_k c'_{k-1}, are kept
-// in the workspace ([k][m][l] pairs, FP64) for m <= ny/2; mode ny - m has the same
-// eigenvalue and reads the pairs of m.
+// 1/p_k, p_k = b_k + lambda_x(l) + lambda_y(m) - a_k c'_{k-1}, c'_k = c_k / p_k, are kept in the
+// workspace ([k][m][l], FP64) for m <= ny/2; mode ny - m has the same eigenvalue and reads those
+// of m.  The solves form c'_k = c_k (1/p_k) again, with the rounding it has here: they are bound
+// by memory, and a stored c' would be as many bytes again.
 __global__ void __launch_bounds__(256) k_thomas_factor(GridP g, const double* __restrict__ pa,
                                                        const double* __restrict__ pb, const double* __restrict__ pc,
                                                        const double* __restrict__ lamx,
-                                                       const double* __restrict__ lamy, double2* __restrict__ pfac) {
+                                                       const double* __restrict__ lamy, double* __restrict__ pfac) {
   const int nxh = g.nx / 2 + 1;
   const int64_t ncol = (int64_t)g.nxp * factor_modes(g);   // l >= nx/2+1 are padding
   const int64_t col = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -570,132 +571,147 @@ __global__ void __launch_bounds__(256) k_thomas_factor(GridP g, const double* __
   if (l >= nxh) return;
   const double lam = lamx[l] + lamy[m];
   // the singular (0, 0) column pins its last unknown: rows 0..nz-2 factorised, the last row
-  // stored as (0, 0) so that the solve returns x = 0 there
+  // stored as 0 so that the solve returns x = 0 there
   const int nr = col == 0 ? g.nz - 1 : g.nz;
   double cprev = 0.0;
   for (int k = 0; k < nr; ++k) {
     const double a = pa[k];
     const double rr = 1.0 / ((pb[k] + lam) - a * cprev);
     const double cc = pc[k] * rr;
-    pfac[(int64_t)k * ncol + col] = make_double2(cc, rr);
+    pfac[(int64_t)k * ncol + col] = rr;
     cprev = cc;
   }
-  if (nr < g.nz) pfac[(int64_t)nr * ncol + col] = make_double2(0.0, 0.0);
+  if (nr < g.nz) pfac[(int64_t)nr * ncol + col] = 0.0;
 }
 
 void launch_thomas_factor(Ctx& c) {
   const int64_t ncol = (int64_t)c.g.nxp * factor_modes(c.g);
   hipLaunchKernelGGL(k_thomas_factor, dim3((unsigned)((ncol + 255) / 256)), dim3(256), 0, c.stream, c.g, c.t.pa,
-                     c.t.pb, c.t.pc, c.t.lamx, c.t.lamy, (double2*)c.t.pfac);
+                     c.t.pb, c.t.pc, c.t.lamx, c.t.lamy, c.t.pfac);
 }
 
-// Launch shape of the chain solves of n rows (nchain chains over all components): segments of
-// S rows (8 up to s8 rows, else 16), P segments per block, CG chains per segment: 64 (a wave
-// per segment, 512 contiguous bytes of each FP64 row) while P <= 16 and the launch still has
-// four blocks per CU, else 32 (nz <= 512).
+// Launch shape of the solves of n rows: segments of S rows (8 up to s8 rows, else 16; the segments
+// are part of the rounding, and FP32 fields keep those they have), P segments per block, CG columns
+// per segment: 64, a wave per segment with scalar loads of its rows' coefficients, up to 12
+// segments (256 x 128 x 96 in FP64 17.7 us, 20.8 with 32 columns), beyond that 32, whose blocks of
+// half the size overlap better (512 x 256 x 128 in FP64 62 us, 72 with 64 columns; 1024 x 512 x
+// 256 in FP32 368 and 375).
 struct ThomasShape {
   int S, CG, P;
 };
-inline ThomasShape thomas_shape(int n, int s8, int64_t nchain) {
+inline ThomasShape thomas_shape(int n, int s8) {
   const int S = n <= s8 ? 8 : 16, P = (n + S - 1) / S;
-  return {S, P <= 16 && nchain / 64 >= 4 * 256 ? 64 : 32, P};
+  return {S, P <= 12 ? 64 : 32, P};
 }
 
 // FP64 z solves of every (l, m) column with the stored factors, by segmented scans
-// (seg_scan_solve).  A column gives two chains (real and imaginary parts), and there are only
-// a few tens of thousands of chains of nz rows: a plain Thomas sweep per chain leaves most of
-// the chip idle behind its dependent chain.  Threads: CG consecutive chains (adjacent in
-// memory, so each row load of a segment group is contiguous) times the segments of S rows.
-// Rows are held in registers, loaded once and stored once.  ZERO (Poisson): the pinned (0, 0) column
-// has its own factor pairs (last row zero); its dzf-weighted mean is removed here and its
-// imaginary part set to zero.  Rows nrow..nz-1 are left as they are (the wall face of w in
-// the Helmholtz solves).
+// (seg_scan_solve): there are only some ten thousand columns of nz rows, and a plain Thomas sweep
+// per column leaves most of the chip idle behind its dependent chain.  Threads: CG consecutive
+// columns (adjacent in memory, so each row load of a segment group is contiguous) times the
+// segments of S rows, real and imaginary parts together (they share the products of the
+// coefficients).  Rows are held in registers, loaded once and stored once.  Bound by memory: with
+// one thread per part, pairs (c', 1/pivot) and loads under a condition, each waited for in turn,
+// 512 x 256 x 128 in FP64 took 85 us, now 62 (305 MB, 4.9 TB/s); 1024 x 512 x 256 in FP32 676,
+// now 368 (1.35 GB, 3.7 TB/s).  ZERO (Poisson): the pinned (0, 0) column has its own factors (last row zero);
+// its dzf-weighted mean is removed here and its imaginary part set to zero.  Rows nrow..nz-1 are
+// left as they are (the wall face of w in the Helmholtz solves).
 template <typename T, int S, int CG, bool ZERO>
 __device__ __forceinline__ void thomas_scan_body(unsigned bx, GridP g, cpx<T>* __restrict__ spec,
-                                                 const double* __restrict__ pa, const double2* __restrict__ pfac,
-                                                 double norm, int nrow) {
-  __shared__ double E[1024 / CG][CG], G[1024 / CG][CG];
-  // with CG a multiple of the wave size a wave holds one segment, whose a_k are then
+                                                 const double* __restrict__ pa, const double* __restrict__ pc,
+                                                 const double* __restrict__ pfac, double norm, int nrow) {
+  __shared__ double2 E[1024 / CG][CG];
+  __shared__ double G[1024 / CG][CG];
+  // with CG a multiple of the wave size a wave holds one segment, whose a_k and c_k are then
   // wave-uniform (scalar loads)
   const int cl = (int)threadIdx.x % CG, P = (int)blockDim.x / CG;
   const int p = CG % 64 == 0 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / CG) : (int)threadIdx.x / CG;
   const int n = nrow, nxh = g.nx / 2 + 1;
-  const int64_t ncol = (int64_t)g.nxp * g.ny, ncol2 = 2 * ncol;
-  const int64_t c2 = (int64_t)bx * CG + cl;
-  const int64_t col = c2 >> 1;
+  const int64_t ncol = (int64_t)g.nxp * g.ny;
+  const int64_t col = (int64_t)bx * CG + cl;
   const int l = (int)(col % g.nxp), m = (int)(col / g.nxp);
-  const bool ok = c2 < ncol2 && l < nxh;
-  // periodic y: mode ny - m uses the pairs of m; ducts: every m has its own
+  const bool ok = col < ncol && l < nxh;
+  // periodic y: mode ny - m uses the factors of m; ducts: every m has its own
   const int mm = (g.ywall || m <= g.ny / 2) ? m : g.ny - m;
   const int64_t nfac = (int64_t)g.nxp * factor_modes(g);
-  const double2* fp = pfac + (ok ? (int64_t)mm * g.nxp + l : 0);
-  T* x = reinterpret_cast<T*>(spec) + (ok ? c2 : 0);
+  const double* fp = pfac + (ok ? (int64_t)mm * g.nxp + l : 0);
+  cpx<T>* x = spec + (ok ? col : 0);
   const int k0 = p * S;
-  double v[S];
-  double2 fc[S];
+  // every load without a condition (rows past the last read it again, columns past the last read
+  // column 0), so that all are in flight together; what they read there is replaced by zeros
+  double2 v[S];
+  double r[S];
+  cpx<T> z[S];
 #pragma unroll
   for (int j = 0; j < S; ++j) {
-    const int k = k0 + j;
-    const bool in = ok && k < n;
-    v[j] = in ? (double)x[(int64_t)k * ncol2] * norm : 0.0;
-    fc[j] = in ? fp[(int64_t)k * nfac] : make_double2(0.0, 0.0);
+    const int k = k0 + j < n ? k0 + j : n - 1;
+    z[j] = x[(int64_t)k * ncol];
+    r[j] = fp[(int64_t)k * nfac];
   }
-  // a_k: scalar loads when a wave holds one segment; else (two segments per wave) from a copy
-  // in LDS, read where used rather than held in registers (the 16-row variant spilled)
-  __shared__ double sa[CG % 64 == 0 ? 1 : 512];
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    const bool in = ok && k0 + j < n;
+    v[j] = in ? make_double2((double)z[j].x * norm, (double)z[j].y * norm) : make_double2(0.0, 0.0);
+    if (!in) r[j] = 0.0;
+  }
+  // a_k, c_k: scalar loads when a wave holds one segment; else (two segments per wave) from a
+  // copy in LDS, read where used rather than held in registers (the 16-row variant spilled)
+  __shared__ double sa[CG % 64 == 0 ? 1 : 512], sc[CG % 64 == 0 ? 1 : 512];
   if constexpr (CG % 64 != 0) {
-    for (int k = (int)threadIdx.x; k < n; k += (int)blockDim.x) sa[k] = pa[k];
+    for (int k = (int)threadIdx.x; k < n; k += (int)blockDim.x) {
+      sa[k] = pa[k];
+      sc[k] = pc[k];
+    }
     __syncthreads();
   }
   auto AF = [&](int j) -> double {
     if constexpr (CG % 64 == 0) return pa[k0 + j];
     else return sa[k0 + j];
   };
-  seg_scan_solve<S, CG>(v, k0, n, p, P, cl, E, G, [&](int j) { return fc[j].y; }, AF, [&](int j) { return fc[j].x; });
+  // c'_k = c_k / p_k
+  auto CF = [&](int j) -> double {
+    if constexpr (CG % 64 == 0) return pc[k0 + j] * r[j];
+    else return sc[k0 + j] * r[j];
+  };
+  seg_scan_solve<S, CG>(v, k0, n, p, P, cl, E, G, [&](int j) { return r[j]; }, AF, CF);
   if (ZERO && bx == 0) {
-    // zero mode: chains 0 (real part) and 1 (imaginary part) of this block
+    // zero mode: column 0 of this block
     double sw = 0.0, sd = 0.0;
 #pragma unroll
     for (int j = 0; j < S; ++j) {
       const int k = k0 + j;
       if (k < n) {
-        sw += v[j] * g.dzf[k + 1];
+        sw += v[j].x * g.dzf[k + 1];
         sd += g.dzf[k + 1];
       }
     }
     __syncthreads();
-    if (cl == 0) {
-      E[p][0] = sw;
-      G[p][0] = sd;
-    }
+    if (cl == 0) E[p][0] = make_double2(sw, sd);
     __syncthreads();
     if (cl == 0) {
       double tw = 0.0, td = 0.0;
       for (int q = 0; q < P; ++q) {
-        tw += E[q][0];
-        td += G[q][0];
+        tw += E[q][0].x;
+        td += E[q][0].y;
       }
       const double mean = tw / td;
 #pragma unroll
-      for (int j = 0; j < S; ++j) v[j] -= mean;
-    } else if (cl == 1) {
-#pragma unroll
-      for (int j = 0; j < S; ++j) v[j] = 0.0;
+      for (int j = 0; j < S; ++j) v[j] = make_double2(v[j].x - mean, 0.0);
     }
   }
   if (ok) {
 #pragma unroll
     for (int j = 0; j < S; ++j) {
       const int k = k0 + j;
-      if (k < n) x[(int64_t)k * ncol2] = (T)v[j];
+      if (k < n) x[(int64_t)k * ncol] = {(T)v[j].x, (T)v[j].y};
     }
   }
 }
 
 template <typename T, int S, int CG, bool ZERO>
 __global__ void __launch_bounds__(1024) k_thomas_scan(GridP g, cpx<T>* __restrict__ spec, const double* __restrict__ pa,
-                                                      const double2* __restrict__ pfac, double norm, int nrow) {
-  thomas_scan_body<T, S, CG, ZERO>(blockIdx.x, g, spec, pa, pfac, norm, nrow);
+                                                      const double* __restrict__ pc, const double* __restrict__ pfac,
+                                                      double norm, int nrow) {
+  thomas_scan_body<T, S, CG, ZERO>(blockIdx.x, g, spec, pa, pc, pfac, norm, nrow);
 }
 
 // ---------------------------------------------------------------- three components at once
@@ -728,29 +744,31 @@ __global__ void __launch_bounds__(256) k_fft_lines3(FftPlan P, cpx<T>* data, int
                                      L, twd, twf, lamx, lamy, lamz, norm, dtp, hg);
 }
 
-// component blockIdx.y: u and v take the u/v rows and factors, w the w rows (nz - 1 unknowns)
+// component blockIdx.y: u and v take the u/v rows and factors, w the w rows (nz - 1 unknowns);
+// hfac: the CN-z rows (a_uv at 6 nz, a_w at 7 nz, c_uv at 9 nz, c_w at 11 nz)
 template <typename T, int S, int CG>
 __global__ void __launch_bounds__(1024) k_thomas_scan3(GridP g, cpx<T>* __restrict__ spec, int64_t cstride,
-                                                       const double* __restrict__ a_uv, const double* __restrict__ a_w,
-                                                       const double2* __restrict__ fac_uv,
-                                                       const double2* __restrict__ fac_w, double norm) {
-  const int comp = blockIdx.y;
-  thomas_scan_body<T, S, CG, false>(blockIdx.x, g, spec + comp * cstride, comp < 2 ? a_uv : a_w,
-                                comp < 2 ? fac_uv : fac_w, norm, comp < 2 ? g.nz : g.nz - 1);
+                                                       const double* __restrict__ hfac,
+                                                       const double* __restrict__ fac_uv,
+                                                       const double* __restrict__ fac_w, double norm) {
+  const int comp = blockIdx.y, n = g.nz;
+  thomas_scan_body<T, S, CG, false>(blockIdx.x, g, spec + comp * cstride, hfac + (comp < 2 ? 6 : 7) * n,
+                                    hfac + (comp < 2 ? 9 : 11) * n, comp < 2 ? fac_uv : fac_w, norm,
+                                    comp < 2 ? n : n - 1);
 }
 
 // Crank-Nicolson in all directions, wall-bounded z (Eq. onestar_imp3d): after FFTs in x and
 // y, every (l, m) column holds the tridiagonal system with rows a_k, b_k - c (lamx(l) +
 // lamy(m)), c_k (c = gamma nu dt / 2; a, b, c the CN-z rows of the component, wall folds
-// included), solved in FP64.  The pivots depend on dt, so the factor pairs (c', 1/pivot) of
-// this substep are formed here, once for the u/v rows and once for the w rows, for m <=
+// included), solved in FP64.  The pivots depend on dt, so their inverses for this substep are
+// formed here, once for the u/v rows and once for the w rows, for m <=
 // ny/2 (mode ny - m has the same eigenvalue); the solves are k_thomas_scan.  One thread per
 // (column, row set).
 __global__ void __launch_bounds__(256) k_helm3d_factor(GridP g, const double* __restrict__ hfac,
                                                        const double* __restrict__ lamx,
                                                        const double* __restrict__ lamy,
                                                        const double* __restrict__ dtp, double hg,
-                                                       double2* __restrict__ fac) {
+                                                       double* __restrict__ fac) {
   const int nxh = g.nx / 2 + 1, n = g.nz;
   const int64_t nfac = (int64_t)g.nxp * (g.ny / 2 + 1);
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -763,13 +781,13 @@ __global__ void __launch_bounds__(256) k_helm3d_factor(GridP g, const double* __
   const double* ra = hfac + (w ? 7 : 6) * n;
   const double* rb = hfac + (w ? 10 : 8) * n;
   const double* rc = hfac + (w ? 11 : 9) * n;
-  double2* f = fac + (w ? (int64_t)n * nfac : 0) + col;
+  double* f = fac + (w ? (int64_t)n * nfac : 0) + col;
   const int nr = w ? n - 1 : n;
   double cprev = 0.0;
   for (int k = 0; k < nr; ++k) {
     const double r = 1.0 / ((rb[k] - shift) - ra[k] * cprev);
     cprev = rc[k] * r;
-    f[(int64_t)k * nfac] = make_double2(cprev, r);
+    f[(int64_t)k * nfac] = r;
   }
 }
 
@@ -950,21 +968,21 @@ static void spectral_solve(Ctx& c) {
   if (c.cfg.zbc == LES_ZBC_PERIODIC) {
     fftz_solve<T>(c, "fftz_solve", 0.0);
   } else {
-    const int64_t nchain = 2 * (int64_t)c.g.nxp * ny;
-    const ThomasShape sh = thomas_shape(nz, 32, nchain);
+    const int64_t ncol = (int64_t)c.g.nxp * ny;
+    const ThomasShape sh = thomas_shape(nz, sizeof(T) == 8 ? 128 : 32);
     const dim3 block(sh.CG * sh.P);
     const double norm = 1.0 / ((double)c.g.nx * ny);
-    const double bytes = 2 * spec_bytes + (double)nxh * factor_modes(c.g) * nz * 16;
+    const double bytes = 2 * spec_bytes + (double)nxh * factor_modes(c.g) * nz * 8;
     auto go = [&](auto kern, int64_t nb) {
-      LES_LAUNCH(c, "thomas_z", bytes, kern, dim3((unsigned)nb), block, 0, c.g, sp, c.t.pa, (const double2*)c.t.pfac,
+      LES_LAUNCH(c, "thomas_z", bytes, kern, dim3((unsigned)nb), block, 0, c.g, sp, c.t.pa, c.t.pc, c.t.pfac,
                  norm, nz);
     };
     if (sh.CG == 64)
-      sh.S == 8 ? go(k_thomas_scan<T, 8, 64, true>, (nchain + 64 - 1) / 64)
-                : go(k_thomas_scan<T, 16, 64, true>, (nchain + 64 - 1) / 64);
+      sh.S == 8 ? go(k_thomas_scan<T, 8, 64, true>, (ncol + 64 - 1) / 64)
+                : go(k_thomas_scan<T, 16, 64, true>, (ncol + 64 - 1) / 64);
     else
-      sh.S == 8 ? go(k_thomas_scan<T, 8, 32, true>, (nchain + 32 - 1) / 32)
-                : go(k_thomas_scan<T, 16, 32, true>, (nchain + 32 - 1) / 32);
+      sh.S == 8 ? go(k_thomas_scan<T, 8, 32, true>, (ncol + 32 - 1) / 32)
+                : go(k_thomas_scan<T, 16, 32, true>, (ncol + 32 - 1) / 32);
   }
   ffty<T, 1>(c, "ffty_inv");
 }
@@ -995,8 +1013,8 @@ void launch_helmholtz_3d(Ctx& c, int stage) {
   const int64_t nfac = (int64_t)c.g.nxp * (ny / 2 + 1);
   const double norm_xy = 1.0 / ((double)nx * ny);
   if (c.cfg.zbc != LES_ZBC_PERIODIC)
-    LES_LAUNCH(c, "h3d_factor", 2.0 * nfac * n * 16, k_helm3d_factor, dim3((unsigned)((2 * nfac + 255) / 256)), dim3(256),
-               0, c.g, c.t.hfac, c.t.lamx, c.t.lamy, c.t.dt, hg, (double2*)c.t.hfac3);
+    LES_LAUNCH(c, "h3d_factor", 2.0 * nfac * n * 8, k_helm3d_factor, dim3((unsigned)((2 * nfac + 255) / 256)), dim3(256),
+               0, c.g, c.t.hfac, c.t.lamx, c.t.lamy, c.t.dt, hg, c.t.hfac3);
   // forward x of the three components
   {
     const FftPlan P = make_plan(nx);
@@ -1022,24 +1040,22 @@ void launch_helmholtz_3d(Ctx& c, int stage) {
                (int64_t)c.g.nxp, Lz, c.t.twz, c.t.twz_f, c.t.lamx, c.t.lamy, c.t.lamz, 1.0 / ((double)nx * ny * n),
                c.t.dt, hg);
   } else {
-    const int64_t nchain = 2 * (int64_t)c.g.nxp * ny;
-    const ThomasShape sh = thomas_shape(n, 128, 3 * nchain);
+    const int64_t ncol = (int64_t)c.g.nxp * ny;
+    const ThomasShape sh = thomas_shape(n, 128);
     const dim3 block(sh.CG * sh.P);
-    const double* a_uv = c.t.hfac + 6 * n;
-    const double* a_w = c.t.hfac + 7 * n;
-    const double2* f_uv = (const double2*)c.t.hfac3;
-    const double2* f_w = f_uv + (int64_t)n * nfac;
-    const double bytes = 6 * spec_bytes + 3.0 * nfac * n * 16;
+    const double* f_uv = c.t.hfac3;
+    const double* f_w = f_uv + (int64_t)n * nfac;
+    const double bytes = 6 * spec_bytes + 3.0 * nfac * n * 8;
     auto go = [&](auto kern, int64_t nb) {
-      LES_LAUNCH(c, "h3d_thomas_z", bytes, kern, dim3((unsigned)nb, 3), block, 0, c.g, sp, cstride, a_uv, a_w, f_uv,
-                 f_w, norm_xy);
+      LES_LAUNCH(c, "h3d_thomas_z", bytes, kern, dim3((unsigned)nb, 3), block, 0, c.g, sp, cstride, c.t.hfac, f_uv, f_w,
+                 norm_xy);
     };
     if (sh.CG == 64)
-      sh.S == 8 ? go(k_thomas_scan3<T, 8, 64>, (nchain + 64 - 1) / 64)
-                : go(k_thomas_scan3<T, 16, 64>, (nchain + 64 - 1) / 64);
+      sh.S == 8 ? go(k_thomas_scan3<T, 8, 64>, (ncol + 64 - 1) / 64)
+                : go(k_thomas_scan3<T, 16, 64>, (ncol + 64 - 1) / 64);
     else
-      sh.S == 8 ? go(k_thomas_scan3<T, 8, 32>, (nchain + 32 - 1) / 32)
-                : go(k_thomas_scan3<T, 16, 32>, (nchain + 32 - 1) / 32);
+      sh.S == 8 ? go(k_thomas_scan3<T, 8, 32>, (ncol + 32 - 1) / 32)
+                : go(k_thomas_scan3<T, 16, 32>, (ncol + 32 - 1) / 32);
   }
   LES_LAUNCH(c, "h3d_ffty_inv", 6 * spec_bytes, (k_fft_lines3<T, 1, false>), gy, dim3(lsy.nt), lsy.sh, Py, sp,
              cstride, nxh, (int64_t)c.g.nxp, (int64_t)c.g.nxp * ny, Ly, c.t.twy, c.t.twy_f, c.t.lamx, c.t.lamy,
