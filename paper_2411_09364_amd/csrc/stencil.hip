@@ -677,101 +677,116 @@ __device__ void helmholtz_factor_body(const GridP& g, double* hfac, const double
   }
 }
 
-// CN-z Helmholtz solves (Eq. onestar_imp1d), staged through LDS: a block takes hc
-// consecutive (j, i) columns of one component, all threads load the m x hc right-hand sides
-// produced by the predictor (coalesced along i, held in double), hc threads run the FP64
-// elimination with the shared factors, all threads store.  The wall-model rows take the
-// lagged wall stress (from u^k) as a known flux.
+// CN-z Helmholtz solves (Eq. onestar_imp1d) of the right-hand sides produced by the predictor: one
+// thread per (j, i) column and component marches up its rows with the shared factors (scalar
+// loads), HB rows in flight ahead of the FP64 elimination, and back down.  The eliminated values of
+// the last HR rows stay in registers, those below in LDS (a double per row and thread, each thread
+// its own: no barrier), which bounds the waves a CU holds.  Bound by the elimination's chain: staged
+// through LDS by 256 threads for 64 that eliminate, the three components of 240 x 120 x 75 in FP32
+// took 43 us, now 18.  The wall-model rows take the lagged wall stress (from u^k) as a known flux.
+constexpr int HC = 64, HR = 32, HB = 16;
+// rows in LDS: whole batches
+__host__ __device__ inline int hz_lds_rows(int m) { return m > HR ? (m - HR + HB - 1) / HB * HB : 0; }
 template <typename T>
-__global__ void __launch_bounds__(256) k_helmholtz(GridP g, T* __restrict__ us, T* __restrict__ vs,
-                                                   T* __restrict__ ws, const double* __restrict__ hfac,
-                                                   const double* __restrict__ tau, const double* __restrict__ dtp,
-                                                   double gamma, int wallmodel, int hc) {
-  extern __shared__ double hsm[];   // [m][hc]
+__global__ void __launch_bounds__(HC) k_helmholtz(GridP g, T* __restrict__ us, T* __restrict__ vs,
+                                                  T* __restrict__ ws, const double* __restrict__ hfac,
+                                                  const double* __restrict__ tau, const double* __restrict__ dtp,
+                                                  double gamma, int wallmodel) {
+  extern __shared__ double hd[];   // [rows below the registers'][blockDim.x]
   const int comp = blockIdx.y;
   const int n = g.nz;
   const int m = comp < 2 ? n : n - 1;
   const int64_t s = g.sxy;
-  const int64_t col0 = (int64_t)blockIdx.x * hc;
-  const int cw = (int)(s - col0 < hc ? s - col0 : hc);
-  T* x = (comp == 0 ? us : (comp == 1 ? vs : ws)) + s + col0;   // plane 1
-  double* fac = hsm + (size_t)m * hc;   // c', 1/pivot, sub-diagonal of this component's rows
-  for (int e = threadIdx.x; e < m; e += blockDim.x) {
-    fac[e] = hfac[(comp < 2 ? 0 : 2 * n) + e];
-    fac[m + e] = hfac[(comp < 2 ? n : 3 * n) + e];
-    fac[2 * m + e] = hfac[(comp < 2 ? 6 * n : 7 * n) + e];
+  const int64_t col = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (col >= s) return;
+  T* x = (comp == 0 ? us : (comp == 1 ? vs : ws)) + s + col;   // row k at x[k s]
+  const double* cp = hfac + (comp < 2 ? 0 : 2 * n);
+  const double* rp = hfac + (comp < 2 ? n : 3 * n);
+  const double* av = hfac + (comp < 2 ? 6 * n : 7 * n);
+  const bool flux = comp < 2 && wallmodel;
+  double f0 = 0.0, f1 = 0.0;   // known fluxes of the first and the last row over c
+  const double c = gamma * g.nu * dtp[0] / 2.0;
+  if (flux) {
+    f0 = -(tau[(comp == 0 ? 0 : 1) * s + col] / g.nu) / g.dzf[1];
+    f1 = -(tau[(comp == 0 ? 2 : 3) * s + col] / g.nu) / g.dzf[n];
   }
-  // loads in batches of HB per thread, all issued before their LDS stores
-  constexpr int HB = 8;
-  const int total = m * hc;
-  for (int e0 = 0; e0 < total; e0 += HB * (int)blockDim.x) {
-    T v[HB];
+  double* hl = hd + threadIdx.x;
+  const int st = (int)blockDim.x;
+  const int k0 = hz_lds_rows(m);   // first row of the registers'
+  T nx[HB];
+  auto fetch = [&](int kb) {
 #pragma unroll
-    for (int b = 0; b < HB; ++b) {
-      const int e = e0 + b * (int)blockDim.x + (int)threadIdx.x;
-      const int k = e / hc, q = e % hc;
-      v[b] = (e < total && q < cw) ? x[(int64_t)k * s + q] : (T)0;
+    for (int j = 0; j < HB; ++j) nx[j] = x[(int64_t)min(kb + j, m - 1) * s];
+  };
+  double dp = 0.0;
+  fetch(0);
+  for (int kb = 0; kb < k0; kb += HB) {
+    T cur[HB];
+    double a8[HB], r8[HB];
+#pragma unroll
+    for (int j = 0; j < HB; ++j) {
+      cur[j] = nx[j];
+      a8[j] = ro_load(av, kb + j);
+      r8[j] = ro_load(rp, kb + j);
     }
+    fetch(kb + HB);
 #pragma unroll
-    for (int b = 0; b < HB; ++b) {
-      const int e = e0 + b * (int)blockDim.x + (int)threadIdx.x;
-      if (e < total) hsm[e] = (double)v[b];
-    }
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < cw) {
-    const int q = threadIdx.x;
-    const double* cp = fac;
-    const double* rp = fac + m;
-    const double* av = fac + 2 * m;
-    double* col = hsm + q;   // row k at col[k hc]
-    if (comp < 2 && wallmodel) {
-      const double c = gamma * g.nu * dtp[0] / 2.0;
-      col[0] += c * (-(tau[(comp == 0 ? 0 : 1) * s + col0 + q] / g.nu) / g.dzf[1]);
-      col[(n - 1) * hc] += c * (-(tau[(comp == 0 ? 2 : 3) * s + col0 + q] / g.nu) / g.dzf[n]);
-    }
-    // rows in chunks of CH, every LDS read of a chunk issued before its chain
-    constexpr int CH = 8;
-    double dp = 0.0;
-    for (int k0 = 0; k0 < m; k0 += CH) {
-      double fv[CH], a8[CH], r8[CH];
-#pragma unroll
-      for (int j = 0; j < CH; ++j) {
-        const int k = k0 + j < m ? k0 + j : m - 1;
-        fv[j] = col[k * hc];
-        a8[j] = av[k];
-        r8[j] = rp[k];
-      }
-#pragma unroll
-      for (int j = 0; j < CH; ++j) {
-        if (k0 + j < m) {
-          dp = (fv[j] - a8[j] * dp) * r8[j];
-          col[(k0 + j) * hc] = dp;
-        }
-      }
-    }
-    double xn = dp;
-    for (int k1 = m - 2; k1 >= 0; k1 -= CH) {
-      double fv[CH], c8[CH];
-#pragma unroll
-      for (int j = 0; j < CH; ++j) {
-        const int k = k1 - j >= 0 ? k1 - j : 0;
-        fv[j] = col[k * hc];
-        c8[j] = cp[k];
-      }
-#pragma unroll
-      for (int j = 0; j < CH; ++j) {
-        if (k1 - j >= 0) {
-          xn = fv[j] - c8[j] * xn;
-          col[(k1 - j) * hc] = xn;
-        }
-      }
+    for (int j = 0; j < HB; ++j) {
+      double f = (double)cur[j];
+      if (j == 0 && flux && kb == 0) f += c * f0;
+      dp = (f - a8[j] * dp) * r8[j];
+      hl[(kb + j) * st] = dp;
     }
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < m * hc; e += blockDim.x) {
-    const int k = e / hc, q = e % hc;
-    if (q < cw) x[(int64_t)k * s + q] = (T)hsm[e];
+  double d[HR];
+#pragma unroll
+  for (int b = 0; b < HR; b += HB) {
+    T cur[HB];
+    double a8[HB], r8[HB];
+#pragma unroll
+    for (int j = 0; j < HB; ++j) {
+      cur[j] = nx[j];
+      a8[j] = ro_load(av, min(k0 + b + j, m - 1));
+      r8[j] = ro_load(rp, min(k0 + b + j, m - 1));
+    }
+    if (b + HB < HR) fetch(k0 + b + HB);
+#pragma unroll
+    for (int j = 0; j < HB; ++j) {
+      const int k = k0 + b + j;
+      double f = (double)cur[j];
+      if (flux && k == 0) f += c * f0;
+      if (flux && k == m - 1) f += c * f1;
+      const double t = (f - a8[j] * dp) * r8[j];
+      dp = k < m ? t : dp;
+      d[b + j] = dp;
+    }
+  }
+  double xn = dp;
+#pragma unroll
+  for (int b = HR - HB; b >= 0; b -= HB) {
+    double c8[HB];
+#pragma unroll
+    for (int j = 0; j < HB; ++j) c8[j] = ro_load(cp, min(k0 + b + j, m - 1));
+#pragma unroll
+    for (int j = HB - 1; j >= 0; --j) {
+      const int k = k0 + b + j;
+      const double t = d[b + j] - c8[j] * xn;
+      xn = k < m - 1 ? t : xn;
+      if (k < m) x[(int64_t)k * s] = (T)xn;
+    }
+  }
+  for (int kb = k0 - HB; kb >= 0; kb -= HB) {
+    double v[HB], c8[HB];
+#pragma unroll
+    for (int j = 0; j < HB; ++j) {
+      v[j] = hl[(kb + j) * st];
+      c8[j] = ro_load(cp, kb + j);
+    }
+#pragma unroll
+    for (int j = HB - 1; j >= 0; --j) {
+      xn = v[j] - c8[j] * xn;
+      x[(int64_t)(kb + j) * s] = (T)xn;
+    }
   }
 }
 
@@ -834,13 +849,12 @@ void launch_helmholtz(Ctx& c, int stage) {
                (T*)c.us, (T*)c.vs, (T*)c.wsf, c.t.hfac, c.pred_kc);
     return;
   }
-  // columns per block: the largest power of two <= 64 whose rows fit 64 KB of LDS
-  int hc = 64;
-  while (hc > 8 && (size_t)c.g.nz * (hc + 3) * sizeof(double) > 65536) hc /= 2;
-  const size_t sh = (size_t)c.g.nz * (hc + 3) * sizeof(double);
-  dim3 block(256), grid((unsigned)((c.g.sxy + hc - 1) / hc), 3);
-  LES_LAUNCH(c, "helmholtz_z", 6.0 * c.g.sxy * c.g.nz * sizeof(T), k_helmholtz<T>, grid, block, sh, c.g, (T*)c.us,
-             (T*)c.vs, (T*)c.wsf, c.t.hfac, c.t.tau, c.t.dt, G[stage], c.cfg.zbc == LES_ZBC_WALLMODEL ? 1 : 0, hc);
+  // a wave of columns per block; half a wave where their LDS rows would pass 128 KB
+  const int rows = hz_lds_rows(c.g.nz), hc = rows <= 256 ? HC : HC / 2;
+  const size_t sh = (size_t)rows * hc * sizeof(double);
+  dim3 grid((unsigned)((c.g.sxy + hc - 1) / hc), 3);
+  LES_LAUNCH(c, "helmholtz_z", 6.0 * c.g.sxy * c.g.nz * sizeof(T), k_helmholtz<T>, grid, dim3(hc), sh, c.g, (T*)c.us,
+             (T*)c.vs, (T*)c.wsf, c.t.hfac, c.t.tau, c.t.dt, G[stage], c.cfg.zbc == LES_ZBC_WALLMODEL ? 1 : 0);
 }
 
 // ============================================================================ boundary planes
