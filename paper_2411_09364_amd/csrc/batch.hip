@@ -110,7 +110,7 @@ les_status prepare(les_batch* b) {
     d.ly = fl[1].per;
     d.lz = fl[2].per;
     d.kc = std::min(b->tune_kc ? b->tune_kc : b->def_kc, nz);
-    d.pkc = c.pred_kc;
+    d.pkc = c.batch_kc;
     d.sgs = c.cfg.sgs;
     auto set = [&](int kind, int x, int y, int z) {
       d.gdim[kind][0] = x;

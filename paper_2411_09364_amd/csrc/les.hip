@@ -262,7 +262,28 @@ size_t carve(Ctx& c, char* base) {
       const int r = std::atoi(e);
       if (r == 8 || r == 16) c.pred_ty = r;
     }
-    c.pred_kc = chunk_rounds(c.pred_ty == 16 ? slots16 : (mixed ? 1024 : 768));
+    const int64_t pslots = c.pred_ty == 16 ? slots16 : (mixed ? 1024 : 768);
+    c.pred_kc = chunk_rounds(pslots);
+    c.batch_kc = c.pred_kc;
+    // launches that make no whole rounds take the chunks with the fewest plane iterations, two planes of a
+    // chunk's start included: 9 of 9 planes over 1080 blocks (240 x 120 x 75, FP32) ran a second round for 56
+    // of them, 38 us, now 31; the 32^3 box has 4 tiles, 16 blocks of 8 planes took 16.5 us, 128 of one plane 7.6;
+    // the duct of 512 x 80 x 80 82 us, now 79
+    if (whole_rounds(pslots) == 0) {
+      // an elimination along the march (FP64, CN in z) pays for each chunk and has HZ_MAXCH at most
+      int64_t low = 1;
+      if (!mixed && f.implicit_z == LES_VISC_CN_Z) {
+        low = std::min<int64_t>(8, n);
+        if ((n + c.pred_kc - 1) / c.pred_kc <= HZ_MAXCH) low = std::max<int64_t>(low, (n + HZ_MAXCH - 1) / HZ_MAXCH);
+      }
+      int64_t best = 0;
+      for (int64_t kc = n; kc >= low; --kc) {
+        const int64_t cost = (t.nblk_xy * ((n + kc - 1) / kc) + pslots - 1) / pslots * (kc + 2);
+        if (best != 0 && cost >= best) continue;
+        best = cost;
+        c.pred_kc = (int)kc;
+      }
+    }
   }
   // ducts: one partial per x line and x tile, [nz][ny][nx/32]
   // per (plane, tile, wave) of the fused dynamic-model kernel, or per (plane, row, x tile)

@@ -118,7 +118,9 @@ __host__ __device__ inline int64_t idx3(const GridP& g, int k, int j, int i) {
 constexpr int dsm_tile_rows(bool fp64) { return fp64 ? 16 : 8; }
 // Blocks of that kernel a CU holds: the LDS of an FP64 block is 156 KB, that of an FP32 block 46 KB
 constexpr int dsm_blocks_per_cu(bool fp64) { return fp64 ? 1 : 3; }
-// Planes its z march spends before the first plane it puts out
+// Most z chunks of a predictor that eliminates along its march (FP64, CN in z with walls)
+constexpr int HZ_MAXCH = 8;
+// Planes the dynamic model's z march spends before the first plane it puts out
 constexpr int DSM_WARM = 3;
 
 // XCD-aware tile order.  Workgroups are dispatched to the 8 XCDs in turn by linear index;
@@ -296,6 +298,7 @@ struct Ctx {
   int dsm_kc = 8;         // planes per z chunk of the fused dynamic-model kernel
   int mlp_kc = 8;         // planes per z chunk of the learned-closure inference kernel
   int pred_kc = 8;        // planes per z chunk of the z-marching predictor
+  int batch_kc = 8;       // the same for a box of a batch, whose boxes fill the chip together
   int pred_ty = 8;        // rows of the predictor's 32-wide tiles: 8 or 16
   // time step: the advective maxima taken by the correction's blocks (unless LES_CFL_PASS=1),
   // usable while the fields are those that correction wrote

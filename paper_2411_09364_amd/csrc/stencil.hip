@@ -11,7 +11,7 @@ namespace les {
 constexpr int kMaxNz = 512;   // largest wall-bounded nz accepted by les_init
 
 __device__ void helmholtz_factor_body(const GridP& g, double* hfac, const double* dtp, double gamma, int wallmodel,
-                                      double* dzf, double* dzc, int tid, int nthr);
+                                      int tid, int nthr);
 
 Launch3 point_launch(const GridP& g, int planes) {
   Launch3 L;
@@ -397,13 +397,10 @@ __global__ void __launch_bounds__(32 * TY, TY == 16 ? (sizeof(T) == 8 ? 1 : 2) :
                                                                         const double* __restrict__ hfw) {
   const dim3 bid = xcd_tile(blockIdx, gridDim);
   __shared__ T ring[3][5][zmarch::Tile<TY>::N1];
-  static_assert(sizeof(ring) >= 2 * (kMaxNz + 2) * sizeof(double), "factorisation scratch");
   if (MODE != VISC_EXPLICIT && fslice && bid.z == 0) {
-    // metric copies of the factorisation in the ring's memory
-    double* fz = reinterpret_cast<double*>(&ring[0][0][0]);
     if (bid.x == 0 && bid.y == 0)
-      helmholtz_factor_body(g, hfac, dtp, gamma, wallmodel, fz, fz + kMaxNz + 2,
-                            threadIdx.y * blockDim.x + threadIdx.x, blockDim.x * blockDim.y);
+      helmholtz_factor_body(g, hfac, dtp, gamma, wallmodel, threadIdx.y * blockDim.x + threadIdx.x,
+                            blockDim.x * blockDim.y);
     return;
   }
   predictor_zm_body<T, MODE, RW, TY>(bid, g, u, v, w, p, nut, coef, ru, rv, rw, us, vs, ws, dtp, alpha, beta,
@@ -429,7 +426,6 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 4) kb_predictor(Batc
 // kernel substitutes back (the z chunks of the march fixed up through the products of the
 // elimination's row multipliers); the chunk corrections are held per thread for at most
 // HZ_MAXCH chunks.  Otherwise the staged solve below runs after the predictor.
-constexpr int HZ_MAXCH = 8;
 template <typename T>
 bool hz_fused(const Ctx& c) {
   return sizeof(T) == 8 && c.cfg.implicit_z == VISC_CN_Z && c.cfg.zbc != LES_ZBC_PERIODIC &&
@@ -605,17 +601,16 @@ void launch_predictor(Ctx& c, int stage) {
 // the u rows (no-slip walls; 1 otherwise).  Layout of hfac: [cp_uv | rp_uv | cp_w | rp_w
 // | q | - | a_uv | a_w | b_uv | c_uv | b_w | c_w | pp_uv | pp_w] each nz long (pp: see
 // k_hz_factor).
-// Runs in one block of nthr threads; dzf/dzc are LDS copies of the metrics.  Thread 0 runs
-// the u/v chain (and the flow-rate profile), thread 64 (thread 0 in small blocks) the w chain.
-__device__ void helmholtz_factor_body(const GridP& g, double* hfac, const double* dtp, double gamma, int wallmodel,
-                                      double* dzf, double* dzc, int tid, int nthr) {
+// Runs in one block of nthr threads, which first form the rows, one each; then thread 0 runs the
+// u/v chain (and the flow-rate profile), thread 64 (thread 0 in small blocks) the w chain, with
+// their rows fetched FB at a time ahead of the divisions.  The chains are all this launch waits for
+// in small FP32 channels and with CN in all directions (rows formed along the chains, metrics and
+// profile read row by row: the predictor of 256 x 128 x 96 with CN in all directions took 80 us, now
+// 75; that of 240 x 120 x 75 in FP32 38, with its chunks of les_init's rule now 31).
+__device__ void helmholtz_factor_body(const GridP& g, double* __restrict__ hfac, const double* __restrict__ dtp,
+                                      double gamma, int wallmodel, int tid, int nthr) {
   const int n = g.nz;
   const int wthread = nthr > 64 ? 64 : 0;
-  for (int k = tid; k < n + 2; k += nthr) {
-    dzf[k] = g.dzf[k];
-    dzc[k] = g.dzc[k];
-  }
-  __syncthreads();
   const double c = gamma * g.nu * dtp[0] / 2.0;
   double* cp_uv = hfac;
   double* rp_uv = hfac + n;
@@ -628,53 +623,84 @@ __device__ void helmholtz_factor_body(const GridP& g, double* hfac, const double
   double* c_uv = hfac + 9 * n;    // directions shifts the diagonal per wavenumber pair)
   double* b_w = hfac + 10 * n;
   double* c_w = hfac + 11 * n;
-  if (tid == 0) {
-    double cprev = 0.0, dp = 0.0;
-    for (int kk = 1; kk <= n; ++kk) {
-      double lo = 1.0 / (dzc[kk - 1] * dzf[kk]);
-      double up = 1.0 / (dzc[kk] * dzf[kk]);
-      double dg = -(lo + up);
-      if (kk == 1) dg += wallmodel ? lo : -lo;
-      if (kk == n) dg += wallmodel ? up : -up;
-      if (kk == 1) lo = 0.0;
-      if (kk == n) up = 0.0;
-      const double a = -c * lo, b = 1.0 - c * dg, cc = -c * up;
-      const double r = 1.0 / (b - a * cprev);
-      rp_uv[kk - 1] = r;
-      a_uv[kk - 1] = a;
-      b_uv[kk - 1] = b;
-      c_uv[kk - 1] = cc;
-      cprev = cc * r;
-      cp_uv[kk - 1] = cprev;
-      // forward sweep of q = H^-1 1 (bulk-forcing profile, no-slip rows) alongside
-      dp = (1.0 - a * dp) * r;
-      qv[kk - 1] = dp;
-    }
-    if (g.zbc == LES_ZBC_NOSLIP) {
-      for (int kk = n - 1; kk >= 1; --kk) qv[kk - 1] = qv[kk - 1] - cp_uv[kk - 1] * qv[kk];
-    } else {
-      for (int kk = 0; kk < n; ++kk) qv[kk] = 1.0;
-    }
-  }
-  if (tid == wthread) {
+  for (int kk = 1 + tid; kk <= n; kk += nthr) {
+    double lo = 1.0 / (g.dzc[kk - 1] * g.dzf[kk]);
+    double up = 1.0 / (g.dzc[kk] * g.dzf[kk]);
+    double dg = -(lo + up);
+    if (kk == 1) dg += wallmodel ? lo : -lo;
+    if (kk == n) dg += wallmodel ? up : -up;
+    if (kk == 1) lo = 0.0;
+    if (kk == n) up = 0.0;
+    a_uv[kk - 1] = -c * lo;
+    b_uv[kk - 1] = 1.0 - c * dg;
+    c_uv[kk - 1] = -c * up;
     const int m = n - 1;
-    double cprev = 0.0;
-    for (int kk = 1; kk <= m; ++kk) {
-      double lo = 1.0 / (dzf[kk] * dzc[kk]);
-      double up = 1.0 / (dzf[kk + 1] * dzc[kk]);
-      const double dg = -(lo + up);
-      if (kk == 1) lo = 0.0;
-      if (kk == m) up = 0.0;
-      const double a = -c * lo, b = 1.0 - c * dg, cc = -c * up;
-      const double r = 1.0 / (b - a * cprev);
-      rp_w[kk - 1] = r;
-      a_w[kk - 1] = a;
-      b_w[kk - 1] = b;
-      c_w[kk - 1] = cc;
-      cprev = cc * r;
-      cp_w[kk - 1] = cprev;
-    }
+    if (kk > m) continue;
+    lo = 1.0 / (g.dzf[kk] * g.dzc[kk]);
+    up = 1.0 / (g.dzf[kk + 1] * g.dzc[kk]);
+    dg = -(lo + up);
+    if (kk == 1) lo = 0.0;
+    if (kk == m) up = 0.0;
+    a_w[kk - 1] = -c * lo;
+    b_w[kk - 1] = 1.0 - c * dg;
+    c_w[kk - 1] = -c * up;
   }
+  __syncthreads();
+  constexpr int FB = 8;
+  auto chain = [&](const double* a_, const double* b_, const double* c_, double* cp, double* rp, double* q, int m) {
+    double na[FB], nb[FB], nc[FB];
+    auto fetch = [&](int k0) {
+#pragma unroll
+      for (int j = 0; j < FB; ++j) {
+        const int k = min(k0 + j, m - 1);
+        na[j] = a_[k], nb[j] = b_[k], nc[j] = c_[k];
+      }
+    };
+    double cprev = 0.0, dp = 0.0;
+    fetch(0);
+    for (int k0 = 0; k0 < m; k0 += FB) {
+      double a[FB], b[FB], cc[FB];
+#pragma unroll
+      for (int j = 0; j < FB; ++j) a[j] = na[j], b[j] = nb[j], cc[j] = nc[j];
+      fetch(k0 + FB);
+#pragma unroll
+      for (int j = 0; j < FB; ++j) {
+        if (k0 + j < m) {
+          const double r = 1.0 / (b[j] - a[j] * cprev);
+          rp[k0 + j] = r;
+          cprev = cc[j] * r;
+          cp[k0 + j] = cprev;
+          if (q) {
+            // forward sweep of q = H^-1 1 (bulk-forcing profile, no-slip rows) alongside
+            dp = (1.0 - a[j] * dp) * r;
+            q[k0 + j] = dp;
+          }
+        }
+      }
+    }
+    if (!q) return;
+    double x = dp;
+    for (int k1 = m - 2; k1 >= 0; k1 -= FB) {
+      double d[FB], cc[FB];
+#pragma unroll
+      for (int j = 0; j < FB; ++j) {
+        const int k = max(k1 - j, 0);
+        d[j] = q[k], cc[j] = cp[k];
+      }
+#pragma unroll
+      for (int j = 0; j < FB; ++j) {
+        if (k1 - j >= 0) {
+          x = d[j] - cc[j] * x;
+          q[k1 - j] = x;
+        }
+      }
+    }
+  };
+  const bool noslip = g.zbc == LES_ZBC_NOSLIP;
+  if (!noslip)
+    for (int k = tid; k < n; k += nthr) qv[k] = 1.0;
+  if (tid == 0) chain(a_uv, b_uv, c_uv, cp_uv, rp_uv, noslip ? qv : nullptr, n);
+  if (tid == wthread) chain(a_w, b_w, c_w, cp_w, rp_w, nullptr, n - 1);
 }
 
 // CN-z Helmholtz solves (Eq. onestar_imp1d) of the right-hand sides produced by the predictor: one
