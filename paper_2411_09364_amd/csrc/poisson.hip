@@ -717,11 +717,72 @@ __global__ void __launch_bounds__(1024) k_thomas_scan(GridP g, cpx<T>* __restric
 // ---------------------------------------------------------------- three components at once
 // The Helmholtz solves of CN in all directions transform u*, v* and w* through three spectrum
 // buffers (cstride apart), so each stage is one launch over all components (blockIdx.y or z).
+// Crank-Nicolson in all directions, wall-bounded z (Eq. onestar_imp3d): after FFTs in x and
+// y, every (l, m) column holds the tridiagonal system with rows a_k, b_k - c (lamx(l) +
+// lamy(m)), c_k (c = gamma nu dt / 2; a, b, c the CN-z rows of the component, wall folds
+// included), solved in FP64.  The pivots depend on dt, so their inverses for this substep are
+// formed here, once for the u/v rows and once for the w rows (nb blocks each), for m <= ny/2
+// (mode ny - m has the same eigenvalue); the solves are k_thomas_scan.  One thread per column,
+// with HFB rows' coefficients (scalar loads) ahead of the chain of divisions that bounds it: 24 us
+// for 256 x 128 x 96 when each row's were loaded in turn, 21 so, nearly all of it on an idle chip:
+// hence beside the forward x transforms (k_rfftx3), the first blocks of their launch.
+constexpr int HFB = 8;
+struct Helm3dArgs {
+  const double *hfac, *lamx, *lamy, *dtp;
+  double hg;
+  double* fac;   // null: periodic z, no factors
+  int nb;        // blocks per row set
+};
+__device__ __forceinline__ void helm3d_factor_body(int bx, const GridP& g, const Helm3dArgs& h) {
+  const double *__restrict__ hfac = h.hfac, *__restrict__ lamx = h.lamx, *__restrict__ lamy = h.lamy;
+  const int nxh = g.nx / 2 + 1, n = g.nz;
+  const int64_t nfac = (int64_t)g.nxp * (g.ny / 2 + 1);
+  const int w = bx >= h.nb;
+  const int64_t col = (bx - w * h.nb) * (int64_t)blockDim.x + threadIdx.x;
+  if (col >= nfac) return;
+  const int l = (int)(col % g.nxp), m = (int)(col / g.nxp);
+  if (l >= nxh) return;
+  const double shift = h.hg * h.dtp[0] * (lamx[l] + lamy[m]);
+  const double* ra = hfac + (w ? 7 : 6) * n;
+  const double* rb = hfac + (w ? 10 : 8) * n;
+  const double* rc = hfac + (w ? 11 : 9) * n;
+  double* __restrict__ f = h.fac + (w ? (int64_t)n * nfac : 0) + col;
+  const int nr = w ? n - 1 : n;
+  double na[HFB], nb[HFB], nc[HFB];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < HFB; ++j) {
+      const int k = min(k0 + j, nr - 1);
+      na[j] = ro_load(ra, k), nb[j] = ro_load(rb, k), nc[j] = ro_load(rc, k);
+    }
+  };
+  double cprev = 0.0;
+  fetch(0);
+  for (int k0 = 0; k0 < nr; k0 += HFB) {
+    double a[HFB], b[HFB], c[HFB];
+#pragma unroll
+    for (int j = 0; j < HFB; ++j) a[j] = na[j], b[j] = nb[j], c[j] = nc[j];
+    fetch(k0 + HFB);
+#pragma unroll
+    for (int j = 0; j < HFB; ++j) {
+      const double r = 1.0 / ((b[j] - shift) - a[j] * cprev);
+      cprev = c[j] * r;
+      if (k0 + j < nr) f[(int64_t)(k0 + j) * nfac] = r;
+    }
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) k_rfftx3(GridP g, FftPlan P, const T* us, const T* vs, const T* ws,
                                                 cpx<T>* spec, int64_t cstride, const double* twd, const float* twf,
-                                                int npair_blk) {
-  const int comp = blockIdx.y;
+                                                int npair_blk, int nblk, Helm3dArgs h) {
+  // walls: the first row of blocks forms the z factors
+  if (h.fac != nullptr && blockIdx.y == 0) {
+    if ((int)blockIdx.x < 2 * h.nb) helm3d_factor_body(blockIdx.x, g, h);
+    return;
+  }
+  if ((int)blockIdx.x >= nblk) return;
+  const int comp = (int)blockIdx.y - (h.fac != nullptr ? 1 : 0);
   const T* f = comp == 0 ? us : (comp == 1 ? vs : ws);
   rfftx_body<T, 1>(dim3(blockIdx.x), g, P, nullptr, nullptr, nullptr, f, spec + comp * cstride, twd, twf, nullptr,
                    1.0, npair_blk, nullptr);
@@ -755,40 +816,6 @@ __global__ void __launch_bounds__(1024) k_thomas_scan3(GridP g, cpx<T>* __restri
   thomas_scan_body<T, S, CG, false>(blockIdx.x, g, spec + comp * cstride, hfac + (comp < 2 ? 6 : 7) * n,
                                     hfac + (comp < 2 ? 9 : 11) * n, comp < 2 ? fac_uv : fac_w, norm,
                                     comp < 2 ? n : n - 1);
-}
-
-// Crank-Nicolson in all directions, wall-bounded z (Eq. onestar_imp3d): after FFTs in x and
-// y, every (l, m) column holds the tridiagonal system with rows a_k, b_k - c (lamx(l) +
-// lamy(m)), c_k (c = gamma nu dt / 2; a, b, c the CN-z rows of the component, wall folds
-// included), solved in FP64.  The pivots depend on dt, so their inverses for this substep are
-// formed here, once for the u/v rows and once for the w rows, for m <=
-// ny/2 (mode ny - m has the same eigenvalue); the solves are k_thomas_scan.  One thread per
-// (column, row set).
-__global__ void __launch_bounds__(256) k_helm3d_factor(GridP g, const double* __restrict__ hfac,
-                                                       const double* __restrict__ lamx,
-                                                       const double* __restrict__ lamy,
-                                                       const double* __restrict__ dtp, double hg,
-                                                       double* __restrict__ fac) {
-  const int nxh = g.nx / 2 + 1, n = g.nz;
-  const int64_t nfac = (int64_t)g.nxp * (g.ny / 2 + 1);
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= 2 * nfac) return;
-  const int w = t >= nfac;
-  const int64_t col = w ? t - nfac : t;
-  const int l = (int)(col % g.nxp), m = (int)(col / g.nxp);
-  if (l >= nxh) return;
-  const double shift = hg * dtp[0] * (lamx[l] + lamy[m]);
-  const double* ra = hfac + (w ? 7 : 6) * n;
-  const double* rb = hfac + (w ? 10 : 8) * n;
-  const double* rc = hfac + (w ? 11 : 9) * n;
-  double* f = fac + (w ? (int64_t)n * nfac : 0) + col;
-  const int nr = w ? n - 1 : n;
-  double cprev = 0.0;
-  for (int k = 0; k < nr; ++k) {
-    const double r = 1.0 / ((rb[k] - shift) - ra[k] * cprev);
-    cprev = rc[k] * r;
-    f[(int64_t)k * nfac] = r;
-  }
 }
 
 // ============================================================================ bulk
@@ -1012,17 +1039,18 @@ void launch_helmholtz_3d(Ctx& c, int stage) {
   cpx<T>* sp = (cpx<T>*)c.spec;
   const int64_t nfac = (int64_t)c.g.nxp * (ny / 2 + 1);
   const double norm_xy = 1.0 / ((double)nx * ny);
-  if (c.cfg.zbc != LES_ZBC_PERIODIC)
-    LES_LAUNCH(c, "h3d_factor", 2.0 * nfac * n * 8, k_helm3d_factor, dim3((unsigned)((2 * nfac + 255) / 256)), dim3(256),
-               0, c.g, c.t.hfac, c.t.lamx, c.t.lamy, c.t.dt, hg, c.t.hfac3);
-  // forward x of the three components
+  // forward x of the three components; walls: the z factors of this substep beside them
   {
     const FftPlan P = make_plan(nx);
     const RowShape rs = row_shape(nx, sizeof(cpx<T>));
     const int64_t npairs = (int64_t)n * (ny / 2);
-    LES_LAUNCH(c, "h3d_rfftx", 3 * (spec_bytes + (double)c.g.sxy * n * sizeof(T)), (k_rfftx3<T>),
-               dim3((unsigned)((npairs + rs.pairs - 1) / rs.pairs), 3), dim3(rs.nt), rs.sh, c.g, P, (const T*)c.us, (const T*)c.vs,
-               (const T*)c.wsf, sp, cstride, c.t.twx, c.t.twx_f, rs.pairs);
+    const int nblk = (int)((npairs + rs.pairs - 1) / rs.pairs);
+    const bool walls = c.cfg.zbc != LES_ZBC_PERIODIC;
+    const Helm3dArgs h{c.t.hfac, c.t.lamx, c.t.lamy, c.t.dt, hg, walls ? c.t.hfac3 : nullptr,
+                       (int)((nfac + rs.nt - 1) / rs.nt)};
+    LES_LAUNCH(c, "h3d_rfftx", 3 * (spec_bytes + (double)c.g.sxy * n * sizeof(T)) + (walls ? 2.0 * nfac * n * 8 : 0.0),
+               (k_rfftx3<T>), dim3((unsigned)(walls ? std::max(nblk, 2 * h.nb) : nblk), walls ? 4 : 3), dim3(rs.nt), rs.sh,
+               c.g, P, (const T*)c.us, (const T*)c.vs, (const T*)c.wsf, sp, cstride, c.t.twx, c.t.twx_f, rs.pairs, nblk, h);
   }
   const FftPlan Py = make_plan(ny);
   const LineShape lsy = line_shape(ny, sizeof(cpx<T>));
