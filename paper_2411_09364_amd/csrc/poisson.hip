@@ -894,36 +894,44 @@ __global__ void k_scalar_ghosts(GridP g, T* f) {
 // ============================================================================ launchers
 // Row pairs per block of the x transforms: blocks of 128 threads (eight pairs of 256 points).
 // 64 and 256 threads, or 256 of which half only load, took 525-750 us where 128 take 475 (forward
-// x of 1024 x 512 x 256 in FP32) and within 2 us of it on 25 MB of 256 x 128 x 96.
+// x of 1024 x 512 x 256 in FP32) and within 2 us of it on 25 MB of 256 x 128 x 96.  Fewer pairs, with
+// more threads to load each, while there would be no block per CU (npairs row pairs in all: a 64^3
+// box has 64 blocks of 32 pairs, forward x 13.1 us in FP64 and 11.7 in FP32; 256 of 8 take 9.7 and 9.0).
 struct RowShape {
   int pairs, nt;
   size_t sh;       // dynamic LDS bytes
 };
-static RowShape row_shape(int n, size_t esz) {
-  const int team = fft_team(n), pairs = std::max(1, 128 / team);
-  return {pairs, pairs * team, (size_t)pairs * fft_pos(n) * esz};
+static RowShape row_shape(int n, size_t esz, int64_t npairs) {
+  int pairs = std::max(1, 128 / fft_team(n));
+  const int nt = pairs * fft_team(n);
+  while (pairs > 1 && npairs / pairs < 256) pairs /= 2;
+  return {pairs, nt, (size_t)pairs * fft_pos(n) * esz};
 }
 
 // Lines per block of the strided transforms: neighbouring values of 128 bytes, one cache line
 // (256 bytes were no faster), more while a block has fewer than 64 threads, fewer where it would
-// have more than 256 (`want`: at most that many, whatever the cache line).
+// have more than 256 (`want`: at most that many, whatever the cache line); down to 64 bytes where
+// `groups` groups of nl lines would leave CUs without a block and a thread has 16 points to take
+// through (z solve of the 64^3 box in FP64 14.5 -> 13.0 us, 32 bytes no faster; of the 32^3 box, 4
+// and 8 points a thread, 8.5 -> 8.7).
 struct LineShape {
   int L, nt;
   size_t sh;
 };
-static LineShape line_shape(int n, size_t esz, int want = 0) {
+static LineShape line_shape(int n, size_t esz, int want = 0, int nl = 1, int64_t groups = 256) {
   const int team = fft_team(n);
   int L = want ? want : (int)(128 / esz);
   while (!want && L * team < 64) L *= 2;
   while (L * team > 256) L /= 2;
+  while (n >= 64 && L * esz > 64 && groups * ((nl + L - 1) / L) < 256) L /= 2;
   return {L, std::max(64, L * team), (size_t)L * fft_pos(n) * esz};
 }
 
 template <typename T>
 static void fwd_x(Ctx& c, int mode, const T* us, const T* vs, const T* ws, const T* fin, double gamma, bool bulk) {
   const FftPlan P = make_plan(c.g.nx);
-  const RowShape rs = row_shape(c.g.nx, sizeof(cpx<T>));
   const int64_t npairs = (int64_t)c.g.nz * (c.g.ny / 2);
+  const RowShape rs = row_shape(c.g.nx, sizeof(cpx<T>), npairs);
   const unsigned nblk = (unsigned)((npairs + rs.pairs - 1) / rs.pairs);
   double* bp = bulk ? c.t.bulk : nullptr;
   const double spec_bytes = (double)(c.g.nx / 2 + 1) * c.g.ny * c.g.nz * 2 * sizeof(T);
@@ -945,7 +953,7 @@ static void ffty(Ctx& c, const char* name) {
   const int ny = c.g.ny, nz = c.g.nz;
   const double spec_bytes = (double)nxh * ny * nz * 2 * sizeof(T);
   const FftPlan P = make_plan(ny);
-  const LineShape ls = line_shape(ny, sizeof(cpx<T>));
+  const LineShape ls = line_shape(ny, sizeof(cpx<T>), 0, nxh, nz);
   const int L = ls.L;
   dim3 grid((nxh + L - 1) / L, nz);
   // ducts: the cosine transform of the wall-bounded y direction
@@ -962,7 +970,7 @@ static void fftz_solve(Ctx& c, const char* name, double hg) {
   const int ny = c.g.ny, nz = c.g.nz;
   const double spec_bytes = (double)nxh * ny * nz * 2 * sizeof(T);
   const FftPlan P = make_plan(nz);
-  const LineShape ls = line_shape(nz, sizeof(cpx<T>));
+  const LineShape ls = line_shape(nz, sizeof(cpx<T>), 0, nxh, ny);
   const int L = ls.L;
   dim3 grid((nxh + L - 1) / L, ny);
   const double norm = 1.0 / ((double)c.g.nx * ny * nz);
@@ -979,7 +987,7 @@ static void spectral_solve(Ctx& c) {
   const double spec_bytes = (double)nxh * ny * nz * 2 * sizeof(T);
   if (c.bulk_nblk > 0) {
     const FftPlan P = make_plan(ny);
-    const LineShape ls = line_shape(ny, sizeof(cpx<T>));
+    const LineShape ls = line_shape(ny, sizeof(cpx<T>), 0, nxh, nz);
     const int L = ls.L;
     dim3 grid((nxh + L - 1) / L, nz + 1);
     const size_t sh = std::max(ls.sh, 3 * 256 * sizeof(double));
@@ -1017,8 +1025,8 @@ static void spectral_solve(Ctx& c) {
 template <typename T>
 static void inv_x(Ctx& c, T* out) {
   const FftPlan P = make_plan(c.g.nx);
-  const RowShape rs = row_shape(c.g.nx, sizeof(cpx<T>));
   const int64_t npairs = (int64_t)c.g.nz * (c.g.ny / 2);
+  const RowShape rs = row_shape(c.g.nx, sizeof(cpx<T>), npairs);
   const unsigned nblk = (unsigned)((npairs + rs.pairs - 1) / rs.pairs);
   const double spec_bytes = (double)(c.g.nx / 2 + 1) * c.g.ny * c.g.nz * 2 * sizeof(T);
   LES_LAUNCH(c, "irfftx", spec_bytes + (double)c.g.sxy * c.g.nz * sizeof(T), (k_irfftx<T>), dim3(nblk),
@@ -1042,8 +1050,8 @@ void launch_helmholtz_3d(Ctx& c, int stage) {
   // forward x of the three components; walls: the z factors of this substep beside them
   {
     const FftPlan P = make_plan(nx);
-    const RowShape rs = row_shape(nx, sizeof(cpx<T>));
     const int64_t npairs = (int64_t)n * (ny / 2);
+    const RowShape rs = row_shape(nx, sizeof(cpx<T>), 3 * npairs);
     const int nblk = (int)((npairs + rs.pairs - 1) / rs.pairs);
     const bool walls = c.cfg.zbc != LES_ZBC_PERIODIC;
     const Helm3dArgs h{c.t.hfac, c.t.lamx, c.t.lamy, c.t.dt, hg, walls ? c.t.hfac3 : nullptr,
@@ -1090,8 +1098,8 @@ void launch_helmholtz_3d(Ctx& c, int stage) {
              c.t.lamz, 1.0, nullptr, 0.0);
   {
     const FftPlan P = make_plan(nx);
-    const RowShape rs = row_shape(nx, sizeof(cpx<T>));
     const int64_t npairs = (int64_t)n * (ny / 2);
+    const RowShape rs = row_shape(nx, sizeof(cpx<T>), 3 * npairs);
     LES_LAUNCH(c, "h3d_irfftx", 3 * (spec_bytes + (double)c.g.sxy * n * sizeof(T)), (k_irfftx3<T>),
                dim3((unsigned)((npairs + rs.pairs - 1) / rs.pairs), 3), dim3(rs.nt), rs.sh, c.g, P, (const cpx<T>*)sp, cstride,
                (T*)c.us, (T*)c.vs, (T*)c.wsf, c.t.twx, c.t.twx_f, rs.pairs);
@@ -1225,7 +1233,7 @@ template void batch_poisson<double>(hipStream_t, const BatchMap&, const int*, co
 
 // shapes of a box in a batch, whose launches take the largest block and LDS of their boxes
 FftLaunch fft_rows(int n, size_t esz) {
-  const RowShape r = row_shape(n, esz);
+  const RowShape r = row_shape(n, esz, INT64_MAX);
   return {r.pairs, r.nt, r.sh};
 }
 FftLaunch fft_lines(int n, size_t esz, int want) {
