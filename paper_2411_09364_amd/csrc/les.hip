@@ -204,8 +204,7 @@ size_t carve(Ctx& c, char* base) {
   t.vd4 = (double*)take(4 * 8);
   t.twc = (double*)take(2 * f.ny * 8);
   t.twc_f = (float*)take(2 * f.ny * 4);
-  // plane partial sums (LM, MM): one per wave of each x-y tile of the fused dynamic-model
-  // kernel (32 x 8 cells, 4 waves)
+  // tiles of 32 x 8 columns
   t.nblk_xy = ((f.nx + 31) / 32) * ((f.ny + 7) / 8);
   {
     // z chunk lengths in units of 32 x 8 tiles on 256 CUs: whole rounds of resident blocks, at
