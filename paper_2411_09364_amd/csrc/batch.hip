@@ -368,8 +368,10 @@ les_status les_batch_step(les_batch* b, double cfl, int use_graph) {
 
 les_status les_batch_autotune(les_batch* b, int substeps, char* report, size_t len) {
   if (!b || substeps < 1) return LES_EINVAL;
-  const int kcs[] = {4, 8, 16, 32};
-  const int ls[] = {4, 8, 16, 32};
+  // 0 first: the defaults, which stay unless a candidate is faster
+  const int kcs[] = {0, 4, 8, 16, 32};
+  const int ls[] = {0, 4, 8, 16, 32};
+  constexpr int ncand = 5;
   auto time_now = [&]() -> double {
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);
@@ -388,12 +390,13 @@ les_status les_batch_autotune(les_batch* b, int substeps, char* report, size_t l
   double best = 1e300;
   int best_kc = 0;
   b->tune_l = 0;
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < ncand; ++q) {
     b->tune_kc = kcs[q];
     b->dirty = true;
     les_status s = prepare(b);
     if (s != LES_OK) return s;
-    run_substep(b, 0);   // warm
+    // warm (the first candidate for as long as one is timed)
+    for (int i = 0; i < (q == 0 ? substeps : 1); ++i) run_substep(b, i % 3);
     const double ms = time_now();
     char tmp[64];
     std::snprintf(tmp, sizeof(tmp), "%s\"%d\": %.4f", q ? ", " : "", kcs[q], ms / substeps);
@@ -407,7 +410,7 @@ les_status les_batch_autotune(les_batch* b, int substeps, char* report, size_t l
   rep += "}, \"lines\": {";
   best = 1e300;
   int best_l = 0;
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < ncand; ++q) {
     b->tune_l = ls[q];
     b->dirty = true;
     les_status s = prepare(b);
