@@ -25,7 +25,8 @@ namespace mlp {
 __global__ void __launch_bounds__(NT) k_mlp_forward(const float* __restrict__ P, const float* __restrict__ x,
                                                     int64_t n, float* __restrict__ y) {
   __shared__ Weights W;
-  __shared__ unsigned short xs[WAVES][64 * FP];
+  __shared__ __align__(16) unsigned short xs[WAVES][64 * FP];
+  static_assert(__alignof__(xs) >= 4, "read by words (lds4)");
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   load_weights(P, W, tid, NT);
   const int64_t s0 = ((int64_t)blockIdx.x * WAVES + wave) * 64;
@@ -48,10 +49,11 @@ __global__ void __launch_bounds__(NT) k_mlp_forward(const float* __restrict__ P,
 __global__ void __launch_bounds__(NT) k_mlp_grad(const float* __restrict__ P, const float* __restrict__ x,
                                                  const float* __restrict__ t, int64_t n, float* __restrict__ part) {
   __shared__ Weights W;
-  __shared__ unsigned short w2t[H * LD2];             // W2^T, rows padded like W2
-  __shared__ unsigned short xs[WAVES][64 * FP];
+  __shared__ __align__(16) unsigned short w2t[H * LD2];   // W2^T, rows padded like W2
+  __shared__ __align__(16) unsigned short xs[WAVES][64 * FP];
   __shared__ __align__(16) unsigned short tr[WAVES][2][H * LD2];  // transposes: [0] dz2b or dz1b, [1] h1b (rows padded)
   static_assert(sizeof(tr) >= WAVES * H * H * sizeof(float), "the waves' sums of W2 fit");
+  static_assert(__alignof__(xs) >= 4 && __alignof__(w2t) >= 4 && __alignof__(tr) >= 4, "read by words (lds4)");
   __shared__ float gs[WAVES][NPARAM + 1 - H * H];   // the waves' sums of the other parameters
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const int r16 = lane % 16, g4 = 4 * (lane / 16);

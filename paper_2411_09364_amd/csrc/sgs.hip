@@ -583,7 +583,8 @@ __device__ __forceinline__ void dsm_fused_body(dim3 bid, int gdx, int gdy, GridP
   constexpr int RX2 = TL::RX2, N2 = TL::N2, RX1 = TL::RX1, RY1 = TL::RY1, N1 = TL::N1, NROW = TL::NROW,
                 NHALO = TL::NHALO;
   if (gate != nullptr && gate[0] == 0) return;   // learned closure: no point fell back
-  __shared__ T vel[3][N2];           // velocity plane q
+  __shared__ __align__(16) T vel[3][N2];   // velocity plane q
+  static_assert(__alignof__(vel) >= 16 && sizeof(vel[0]) % 16 == 0, "16-byte parts of a plane, straight from memory");
   __shared__ Pack qb[NP][N1];        // filter inputs of plane p
   __shared__ Pack xb[NP][RY1 * TX];  // their x sums
   __shared__ T ut[3][N1];            // filtered velocity of plane p (times 64)
