@@ -129,9 +129,9 @@ __device__ inline void store_nut(const GridP& g, T* nut, int k, int j, int i, T 
 // load and index instructions, not by its bytes: with a thread per cell and every ghost rule
 // checked at every point a duct of 512 x 80 x 80 in FP64 took 62 us, now 42, 240 x 120 x 75 in
 // FP32 27, now 18 (2 and 8 planes a thread: 47 and 43, 20 and 18).  The values that
-// the wall model extrapolates follow from the ones at hand.  Sums of two products are fused as
-// centre_strain's are compiled (the first product into the rounded second one), so that both
-// give the same bits.
+// the wall model extrapolates follow from the ones at hand.  Sums of two products name their fused
+// multiply-adds (the first product into the rounded second one): left to the compiler, the choice may
+// change with the code around, and a batch and a single context have to agree to the last bit.
 constexpr int STRAIN_KZ = 4;
 
 template <typename T>
@@ -1508,6 +1508,7 @@ __global__ void __launch_bounds__(256) kb_dsm_reduce(BatchMap m) {
                      nullptr, (T*)nullptr);
 }
 
+// One plane of a box per thread, by the single context's code: batch and single context agree to the last bit.
 template <typename T>
 __global__ void __launch_bounds__(256) kb_strain_mag(BatchMap m) {
   int box;
@@ -1517,9 +1518,7 @@ __global__ void __launch_bounds__(256) kb_strain_mag(BatchMap m) {
   const int j = bid.y * blockDim.y + threadIdx.y;
   const int k = bid.z + 1;
   if (i >= d.g.nx || j >= d.g.ny) return;
-  T s[6];
-  centre_strain(d.g, (const T*)d.u, (const T*)d.v, (const T*)d.w, k, j, i, s);
-  store_nut(d.g, (T*)d.nut, k, j, i, strain_mag(s));
+  strain_column(d.g, (const T*)d.u, (const T*)d.v, (const T*)d.w, (T*)d.nut, nullptr, j, i, k, k + 1);
 }
 
 // ============================================================================ learned closure
