@@ -425,7 +425,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 4) kb_predictor(Batc
 // CN in z with walls, FP64: the predictor eliminates along its z march and a streaming
 // kernel substitutes back (the z chunks of the march fixed up through the products of the
 // elimination's row multipliers); the chunk corrections are held per thread for at most
-// HZ_MAXCH chunks.  Otherwise the staged solve below runs after the predictor.
+// HZ_MAXCH chunks.  Otherwise the column solves (k_helmholtz) run after the predictor.
 template <typename T>
 bool hz_fused(const Ctx& c) {
   return sizeof(T) == 8 && c.cfg.implicit_z == VISC_CN_Z && c.cfg.zbc != LES_ZBC_PERIODIC &&
@@ -597,8 +597,8 @@ void launch_predictor(Ctx& c, int stage) {
 // ============================================================================ CN in z
 // The matrix (1 - c L_zz), c = gamma nu dt / 2, is the same for every (i, j) column, so
 // its Thomas factorisation (pivots and normalised super-diagonal) is computed once per
-// substep by three threads: u/v rows, w rows, and the flow-rate profile q = H^-1 1 of
-// the u rows (no-slip walls; 1 otherwise).  Layout of hfac: [cp_uv | rp_uv | cp_w | rp_w
+// substep: u/v rows, w rows, and the flow-rate profile q = H^-1 1 of the u rows (no-slip
+// walls; 1 otherwise).  Layout of hfac: [cp_uv | rp_uv | cp_w | rp_w
 // | q | - | a_uv | a_w | b_uv | c_uv | b_w | c_w | pp_uv | pp_w] each nz long (pp: see
 // k_hz_factor).
 // Runs in one block of nthr threads, which first form the rows, one each; then thread 0 runs the
@@ -709,7 +709,9 @@ __device__ void helmholtz_factor_body(const GridP& g, double* __restrict__ hfac,
 // the last HR rows stay in registers, those below in LDS (a double per row and thread, each thread
 // its own: no barrier), which bounds the waves a CU holds.  Bound by the elimination's chain: staged
 // through LDS by 256 threads for 64 that eliminate, the three components of 240 x 120 x 75 in FP32
-// took 43 us, now 18.  The wall-model rows take the lagged wall stress (from u^k) as a known flux.
+// took 43 us, now 18.  Taller columns leave a CU fewer waves, in either form: 160 x 96 x 128, 256 and 512
+// 48, 118 and 511 us staged, now 22, 69 and 228; 512 x 256 x 256 970, now 543.  The wall-model rows take
+// the lagged wall stress (from u^k) as a known flux.
 constexpr int HC = 64, HR = 32, HB = 16;
 // rows in LDS: whole batches
 __host__ __device__ inline int hz_lds_rows(int m) { return m > HR ? (m - HR + HB - 1) / HB * HB : 0; }
