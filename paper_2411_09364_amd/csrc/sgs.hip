@@ -463,12 +463,13 @@ __global__ void __launch_bounds__(256) k_dsm_reduce(GridP g, const double* part,
 // of either velocity makes the z difference across the wall that of the next edge inward (wall
 // model, linear extrapolation) or twice the cell's own value (no-slip, odd).
 // Bound by latency at two waves per SIMD in FP64 (156 KB of LDS and 256 registers: one block of 32 x 16
-// cells per CU; VALU busy 36 %, LDS 45 %) and by VALU issue at three in FP32 (32 x 8 cells, three blocks per
-// CU).  512x256x128 FP64 with the wall model: 601 -> 505 us, against 596 us for 15 inputs through a 9-point
-// filter with all four edges of a cell worked out; 256x128x96: 127 -> 112; 64 boxes of 32^3 to 96^3 in FP32:
-// 4614 -> 3909 us a step; 512x80x80 duct: 217 -> 147.  Measured and dropped in FP64: 32 x 8 tiles at two blocks per CU (572: the halo's
-// share), x sums by lane shifts in place of LDS (508), separate waves for halo points on 32 x 12 tiles (612)
-// or for the model on 16 waves (884, spills), the halo points after the first barrier (586).
+// cells per CU; the VALU busy 36 % of the time, a wave waiting for 44 % of its own and ready but not issued for
+// 22 %) and by VALU issue at three in FP32 (32 x 8 cells, three blocks per CU; VALU busy 69 to 73 %).
+// 512x256x128 FP64 with the wall model: 601 -> 505 us, against 596 us for 15 inputs through a 9-point filter with
+// all four edges of a cell worked out; 256x128x96: 127 -> 112; 64 boxes of 32^3 to 96^3 in FP32: 4614 -> 3909 us a
+// step; 512x80x80 duct: 217 -> 147.  Measured and dropped in FP64: 32 x 8 tiles at two blocks per CU (572: the
+// halo's share), x sums by lane shifts in place of LDS (508), separate waves for halo points on 32 x 12 tiles
+// (612) or for the model on 16 waves (884, spills), the halo points after the first barrier (586).
 namespace fused {
 constexpr int TX = 32;
 constexpr int NQ = 12;   // filter inputs per cell
@@ -972,8 +973,8 @@ __global__ void __launch_bounds__(fused::Tile<T>::NT, fused::Tile<T>::WEU) k_dsm
 // difference of nearly equal FP32 values, so either kernel's c_s is off by some 1e-7 (between walls up to 5e-4),
 // and the pressure of an FP32 run answers the last bits of the eddy viscosity: by 3e-4 of itself in a channel
 // (1024x512x256) and 3e-5 in a 256^3 box with Crank-Nicolson in all directions, as much as its distance from a
-// 64-bit solution, but by 1e-6 in periodic boxes with explicit viscous terms at any size.  The kernel above is faster
-// (3217 -> 2223 us on that channel) and not closer (2.9e-4 against 2.2e-4), so in FP32 only the last take it.
+// 64-bit solution, but by 1.3e-6 in periodic boxes with explicit viscous terms (32^3 to 256^3).  The kernel above is
+// faster (3217 -> 2223 us on that channel) and not closer (2.9e-4 against 2.2e-4), so in FP32 only the last take it.
 //   LDS: velocity of planes p, p + 1 on the tile + 2 halo (strain ghosts substituted), the 15 filter inputs (u_i,
 //        u_i u_j, |S| S_ij at cell centres) of plane p on the tile + 1 halo in pairs, the test-filtered
 //        staggered velocity of two planes on the tile + 1 halo.
